@@ -462,6 +462,21 @@ void dirichlet_tables(const Resolved& r, const std::vector<double>& vel, std::ve
     }
 }
 
+// Threads per face of the face closure.  One is enough where the faces alone
+// give every SIMD four waves (256 CUs x 4 SIMDs x 4 x 64 threads: the 3-D
+// workload's 7.9e5 faces take 0.11 ms); otherwise the smallest group that
+// reaches that many threads, but none whose threads would get fewer than two
+// of a face's nodes or slices.
+int close_lanes(const Resolved& r) {
+    constexpr long long FILL = 256 * 4 * 4 * 64;
+    const long long faces = r.NE * r.D;
+    const int serial = std::max(r.nslices, std::max(r.nv[0], std::max(r.nv[1], r.nv[2])));
+    if (faces >= FILL) return 1;
+    int l = 4;
+    while (l < WG && faces * l < FILL && 8 * l <= serial) l *= 4;
+    return l;
+}
+
 void fill_problem(const Resolved& r, char* base, Problem& P) {
     std::memset(&P, 0, sizeof P);
     P.D = r.D;
@@ -510,6 +525,7 @@ void fill_problem(const Resolved& r, char* base, Problem& P) {
     P.rows = r.storage == CDUGKS_STORE_F32_BF16TAIL ? (const long long*)(base + r.off_rows) : nullptr;
     P.recon = r.recon;
     P.tile = r.tile;
+    P.close_lanes = close_lanes(r);
     P.has_accel = r.has_accel ? 1 : 0;
     for (int d = 0; d < 3; ++d) P.accel[d] = r.accel[d];
 }
@@ -568,7 +584,6 @@ hipError_t enqueue_step(const Problem& P, hipStream_t s) {
     hipError_t e;
     if ((e = launch_face_sums(P, s)) != hipSuccess) return e;
     if ((e = launch_face_close(P, s)) != hipSuccess) return e;
-    if ((e = launch_cell_close(P, s)) != hipSuccess) return e;
     return launch_update(P, s);
 }
 
@@ -972,8 +987,8 @@ int cdugks_info(cdugks_ctx* c, double* dt, double* t, int64_t* steps) {
 int cdugks_profile_phases(cdugks_ctx* c, int64_t nsteps, double* ms) {
     if (!c || !ms || nsteps <= 0) return fail(CDUGKS_ERR_INVALID, "bad argument");
     if (c->sticky) return fail(c->sticky, "context is in an error state");
-    hipEvent_t ev[5];
-    for (int k = 0; k < 5; ++k)
+    hipEvent_t ev[4];
+    for (int k = 0; k < 4; ++k)
         if (hipEventCreate(&ev[k]) != hipSuccess) return fail(CDUGKS_ERR_DEVICE, "event create");
     double acc[4] = {0, 0, 0, 0};
     hipError_t e = hipSuccess;
@@ -985,20 +1000,19 @@ int cdugks_profile_phases(cdugks_ctx* c, int64_t nsteps, double* ms) {
         if (e == hipSuccess) e = hipEventRecord(ev[1], c->stream);
         if (e == hipSuccess) e = launch_face_close(P, c->stream);
         if (e == hipSuccess) e = hipEventRecord(ev[2], c->stream);
-        if (e == hipSuccess) e = launch_cell_close(P, c->stream);
-        if (e == hipSuccess) e = hipEventRecord(ev[3], c->stream);
         if (e == hipSuccess) e = launch_update(P, c->stream);
-        if (e == hipSuccess) e = hipEventRecord(ev[4], c->stream);
-        if (e == hipSuccess) e = hipEventSynchronize(ev[4]);
-        for (int k = 0; k < 4 && e == hipSuccess; ++k) {
+        if (e == hipSuccess) e = hipEventRecord(ev[3], c->stream);
+        if (e == hipSuccess) e = hipEventSynchronize(ev[3]);
+        // ms[2], the cell closure, is part of the update's launch: zero
+        for (int k = 0; k < 3 && e == hipSuccess; ++k) {
             float t = 0.f;
             e = hipEventElapsedTime(&t, ev[k], ev[k + 1]);
-            acc[k] += t;
+            acc[k == 2 ? 3 : k] += t;
         }
         c->cur = 1 - c->cur;
         c->steps += 1;
     }
-    for (int k = 0; k < 5; ++k) (void)hipEventDestroy(ev[k]);
+    for (int k = 0; k < 4; ++k) (void)hipEventDestroy(ev[k]);
     if (e != hipSuccess) return hip_fail(e, "profiled step");
     for (int k = 0; k < 4; ++k) ms[k] = acc[k] / (double)nsteps;
     return cdugks_sync(c);

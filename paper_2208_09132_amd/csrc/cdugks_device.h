@@ -263,9 +263,11 @@ struct Prim {
     bool bad;
 };
 
-__device__ Prim primitives(const Problem& P, const double* Wv) {
+// mu = mu_ref (T/T_ref)^omega; the hard-sphere exponent 1/2 (the usual one)
+// takes the square root, which is exact to half an ulp and a fraction of the
+// general power's instructions.
+__device__ __forceinline__ Prim primitives(const Problem& P, int D, const double* Wv) {
     Prim q;
-    const int D = P.D;
     q.rho = Wv[0];
     double u2 = 0.0;
     for (int d = 0; d < 3; ++d) {
@@ -276,7 +278,8 @@ __device__ Prim primitives(const Problem& P, const double* Wv) {
     double T = (P.gamma - 1.0) / P.R * (E - 0.5 * u2);
     q.RT = P.R * T;
     if (P.relax == 0) {
-        double mu = P.mu_ref * pow(T / P.T_ref, P.omega);
+        const double t = T / P.T_ref;
+        const double mu = P.mu_ref * (P.omega == 0.5 ? sqrt(t) : pow(t, P.omega));
         q.inv_tau_g = q.rho * q.RT / mu;
     } else {
         q.inv_tau_g = P.tau_inv;
@@ -286,25 +289,42 @@ __device__ Prim primitives(const Problem& P, const double* Wv) {
     return q;
 }
 
-__device__ __forceinline__ double maxwell_prefactor(const Problem& P, double rho, double RT) {
+__device__ __forceinline__ double maxwell_prefactor(int D, double rho, double RT) {
     double two_pi_rt = 2.0 * M_PI * RT;
-    double f = P.D == 1 ? 1.0 / sqrt(two_pi_rt)
-                        : (P.D == 2 ? 1.0 / two_pi_rt : 1.0 / (two_pi_rt * sqrt(two_pi_rt)));
+    double f = D == 1 ? 1.0 / sqrt(two_pi_rt)
+                      : (D == 2 ? 1.0 / two_pi_rt : 1.0 / (two_pi_rt * sqrt(two_pi_rt)));
     return rho * f;
 }
 
-__device__ void write_cell_coefs(const Problem& P, double* Pc, long long N, long long c, const Prim& q) {
-    double beta = 0.25 * P.dt * q.inv_tau_g;
-    Pc[PC_A * N + c] = maxwell_prefactor(P, q.rho, q.RT);
-    Pc[PC_INV2RT * N + c] = 0.5 / q.RT;
-    Pc[PC_CRT2 * N + c] = 0.5 * P.c_int * q.RT;
-    Pc[PC_BETA * N + c] = beta;
-    Pc[PC_BETAB * N + c] = beta * P.Pr;
-    Pc[PC_ETA * N + c] = beta * (P.Pr - 1.0);
-    Pc[PC_HU2 * N + c] = 0.5 * (q.u[0] * q.u[0] + q.u[1] * q.u[1] + q.u[2] * q.u[2]);
-    for (int d = 0; d < 3; ++d) Pc[(PC_U0 + d) * N + c] = q.u[d];
+struct CellCoef {
+    double A, inv2RT, cRT2, beta, betab, eta, hu2, u[3];
+};
+
+__device__ __forceinline__ CellCoef cell_coefs(const Problem& P, int D, const Prim& q) {
+    CellCoef k;
+    k.A = maxwell_prefactor(D, q.rho, q.RT);
+    k.inv2RT = 0.5 / q.RT;
+    k.cRT2 = 0.5 * P.c_int * q.RT;
+    k.beta = 0.25 * P.dt * q.inv_tau_g;
+    k.betab = k.beta * P.Pr;
+    k.eta = k.beta * (P.Pr - 1.0);
+    k.hu2 = 0.5 * (q.u[0] * q.u[0] + q.u[1] * q.u[1] + q.u[2] * q.u[2]);
+#pragma unroll
+    for (int d = 0; d < 3; ++d) k.u[d] = q.u[d];
+    return k;
 }
 
+__device__ __forceinline__ void store_coef(double* Pc, long long N, long long c, const CellCoef& k) {
+    Pc[PC_A * N + c] = k.A;
+    Pc[PC_INV2RT * N + c] = k.inv2RT;
+    Pc[PC_CRT2 * N + c] = k.cRT2;
+    Pc[PC_BETA * N + c] = k.beta;
+    Pc[PC_BETAB * N + c] = k.betab;
+    Pc[PC_ETA * N + c] = k.eta;
+    Pc[PC_HU2 * N + c] = k.hu2;
+#pragma unroll
+    for (int d = 0; d < 3; ++d) Pc[(PC_U0 + d) * N + c] = k.u[d];
+}
 
 // ---------------------------------------------------------------------------
 // tile kernels
@@ -344,10 +364,6 @@ struct Geo {
     __device__ static constexpr int SA(int e) { return e == 0 ? 1 : (e == 1 ? AX : AX * AY); }
     __device__ static int qidx(int x, int y, int z) { return (x + OQX) + QX * ((y + OQY) + QY * (z + OQZ)); }
     __device__ static int aidx(int x, int y, int z) { return (x + OAX) + AX * ((y + OAY) + AY * (z + OAZ)); }
-};
-
-struct CellCoef {
-    double A, inv2RT, cRT2, beta, betab, eta, hu2, u[3];
 };
 
 __device__ __forceinline__ CellCoef load_coef(const double* Pc, long long N, long long c) {
@@ -1010,6 +1026,67 @@ struct FaceSumKernel {
 };
 
 // ---------------------------------------------------------------------------
+// cell closure: W^{n+1} = W^n - dt sum_d (G_right - G_left)/dx_d; coefs at n+1
+// ---------------------------------------------------------------------------
+// Part of the single-problem update kernel: each of a cell's update threads
+// (one per velocity slice) forms W^{n+1} and the coefficients it needs for
+// itself, and the one of slice 0 (store) writes them for the next step.  The
+// D + 2 flux moments of 2D faces are a few loads against hundreds of
+// velocities, where a launch of its own cost 4 us of a 52 us step of the Sod
+// tube and 13 us of 1.40 ms of the 256^2 x 28^2 step.  In the batched update
+// the same code raised the FP32 2-D class from 165 to 231 registers (3 waves
+// per SIMD to 2), so batches keep the launch (one for all problems, under 1%
+// of their step).  fl, fr: the cell's left and right faces.
+// The left and right faces of cell c along each d (periodic wrap at the right
+// end).  Cell and face indices fit 31 bits (checked at set-up).
+template <int D>
+__device__ __forceinline__ void cell_faces(const Problem& P, unsigned c, unsigned (&fl)[D], unsigned (&fr)[D]) {
+    const unsigned n0 = P.n[0], n1 = P.n[1], e0 = P.ne[0], e1 = P.ne[1];
+    const unsigned co[3] = {c % n0, D >= 2 ? (c / n0) % n1 : 0, D >= 3 ? c / (n0 * n1) : 0};
+    const unsigned stride[3] = {1, e0, e0 * e1};
+    const unsigned f = co[0] + e0 * (co[1] + e1 * co[2]);
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+        const bool wrap = P.bc[d] == 0 && co[d] + 1 == (unsigned)P.n[d];
+        fl[d] = f;
+        fr[d] = wrap ? f - co[d] * stride[d] : f + stride[d];
+    }
+}
+
+template <int D>
+__device__ __forceinline__ CellCoef cell_close(const Problem& P, long long c, const unsigned (&fl)[D],
+                                               const unsigned (&fr)[D], bool store) {
+    const long long N = P.N, NE = P.NE;
+    double Wn[D + 2], W0[D + 2];
+#pragma unroll
+    for (int k = 0; k < D + 2; ++k) W0[k] = Wn[k] = P.W_in[k * N + c];
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+        const double* Gd = P.G + (long long)d * (D + 2) * NE;
+#pragma unroll
+        for (int k = 0; k < D + 2; ++k)
+            Wn[k] -= P.dt * P.inv_dx[d] * (Gd[k * NE + fr[d]] - Gd[k * NE + fl[d]]);
+    }
+    if (P.has_accel) {
+        // source integrals at t_n (eqs. rhouupdate, rhoEupdate): rho a, (rho u).a
+#pragma unroll
+        for (int e = 0; e < D; ++e) {
+            Wn[1 + e] += P.dt * W0[0] * P.accel[e];
+            Wn[D + 1] += P.dt * W0[1 + e] * P.accel[e];
+        }
+    }
+    const Prim q = primitives(P, D, Wn);
+    if (q.bad) raise_error(P.err);
+    const CellCoef k = cell_coefs(P, D, q);
+    if (store) {
+#pragma unroll
+        for (int e = 0; e < D + 2; ++e) P.W_out[e * N + c] = Wn[e];
+        store_coef(P.P_out, N, c, k);
+    }
+    return k;
+}
+
+// ---------------------------------------------------------------------------
 // update kernel: streaming, one thread per cell over a velocity slice.
 // Reads phi^n and the stored phi_bar at the cell's 2D faces, inverts eq.
 // phibar with the face coefficients, forms the microflux (eq. flux) and writes
@@ -1022,35 +1099,21 @@ struct FaceSumKernel {
 // 1 only its FP32 rows, 2 only its BF16 rows.  The 3-D single-problem step
 // runs the two row kinds as two launches, so that each holds one loop body
 // (see launch_update).
-template <int D, typename ST, bool ACC = false, int ROWS = 0>
+// CLOSE: the kernel closes its cells itself (cell_close); otherwise it loads
+// the coefficients at n+1.
+template <int D, typename ST, bool ACC = false, int ROWS = 0, bool CLOSE = true>
 struct UpdateKernel {
     using CT = typename StoreT<ST>::C;  // stored face values
     __device__ static void run(const Problem& P, long long c, int slice, int nslices) {
         const long long N = P.N, NE = P.NE;
         const bool inside = c < N;
         const long long cc = inside ? c : 0;
-        int co[3];
-        {
-            long long r = cc;
-#pragma unroll
-            for (int e = 0; e < 3; ++e) {
-                co[e] = (int)(r % P.n[e]);
-                r /= P.n[e];
-            }
-        }
-        // left and right faces along each d (periodic wrap at the right end);
-        // face indices fit 32 bits (checked at set-up)
         unsigned fl[D], fr[D];
-#pragma unroll
-        for (int d = 0; d < D; ++d) {
-            int rc[3] = {co[0], co[1], co[2]};
-            fl[d] = (unsigned)(rc[0] + (long long)P.ne[0] * (rc[1] + (long long)P.ne[1] * rc[2]));
-            rc[d] += 1;
-            if (P.bc[d] == 0 && rc[d] == P.n[d]) rc[d] = 0;
-            fr[d] = (unsigned)(rc[0] + (long long)P.ne[0] * (rc[1] + (long long)P.ne[1] * rc[2]));
-        }
+        cell_faces<D>(P, (unsigned)cc, fl, fr);
         const CellCoef k0 = load_coef(P.P_in, N, cc);
-        const CellCoef k1 = load_coef(P.P_out, N, cc);
+        CellCoef k1;
+        if constexpr (CLOSE) k1 = cell_close<D>(P, cc, fl, fr, inside && slice == 0 && ROWS != 2);
+        else k1 = load_coef(P.P_out, N, cc);
         FaceCoef<D> fcl[D], fcr[D];
 #pragma unroll
         for (int d = 0; d < D; ++d) {
@@ -1723,97 +1786,154 @@ __device__ __forceinline__ T load_uniform(const T* p) {
 }
 
 // ---------------------------------------------------------------------------
-// face closure: W_f, coefficients, flux moments (one thread per (d, face))
+// face closure: W_f, coefficients, flux moments; L threads per (d, face)
 // ---------------------------------------------------------------------------
-__device__ void face_close_one(const Problem& P, long long idx) {
-    const int D = P.D;
-    const long long NE = P.NE;
-    if (idx >= NE * D) return;
-    const int d = (int)(idx / NE);
-    const long long f = idx - (long long)d * NE;
-    long long r = f;
-    int cc[3];
-    for (int e = 0; e < 3; ++e) {
-        cc[e] = (int)(r % P.ne[e]);
-        r /= P.ne[e];
+// The serial part of a face is the sum over the velocity slices' partial sums
+// and, per velocity axis, an exponential and five products per node.  L
+// neighbouring threads (a power of 4 up to the workgroup) share both: thread l
+// takes slices and nodes l, l + L, ..., and a butterfly over the group leaves
+// the same sums in every thread.  L is fixed per problem (close_lanes on the
+// host), so a face's sums are formed in the same order in every launch form.
+// With one thread per face a step of the 128 x 16385 sine wave spent 2.86 ms
+// of its 3.31 ms here, at 1/500 of the device's threads.
+template <int L>
+__device__ __forceinline__ double group_sum(double v, double* red) {
+    constexpr int W = L < 64 ? L : 64;
+#pragma unroll
+    for (int m = 1; m < W; m <<= 1) v += __shfl_xor(v, m, 64);
+    if constexpr (L > 64) {
+        // across the waves of the workgroup, in wave order
+        const int w = threadIdx.x >> 6;
+        if ((threadIdx.x & 63) == 0) red[w] = v;
+        __syncthreads();
+        v = red[0];
+#pragma unroll
+        for (int k = 1; k < L / 64; ++k) v += red[k];
+        __syncthreads();
     }
-    for (int e = 0; e < D; ++e)
-        if (e != d && cc[e] >= P.n[e]) return;
-    if (P.bc[d] == 0 && cc[d] >= P.n[d]) return;
+    return v;
+}
 
-    const int NS = 2 * D + 3;
-    double S[MAX_NSUM];
+// thread t of the problem's closure threads; with L > 64 the group is the
+// workgroup, whose threads all call this together
+template <int D, int L>
+__device__ __forceinline__ void face_close_group(const Problem& P, long long t, double* red) {
+    const unsigned NE = (unsigned)P.NE;
+    const long long idx = t / L;
+    const int lane = (int)(threadIdx.x % L);
+    if (idx >= (long long)NE * D) return;
+    const int d = (int)(idx / NE);
+    const unsigned f = (unsigned)(idx - (long long)d * NE);
+    {
+        const unsigned ne0 = P.ne[0], ne1 = P.ne[1];
+        const unsigned cc[3] = {f % ne0, (f / ne0) % ne1, f / (ne0 * ne1)};
+#pragma unroll
+        for (int e = 0; e < D; ++e)
+            if (e != d && cc[e] >= (unsigned)P.n[e]) return;
+        const unsigned cd = d == 0 ? cc[0] : (d == 1 ? cc[1] : cc[2]);
+        if (P.bc[d] == 0 && cd >= (unsigned)P.n[d]) return;
+    }
+
+    constexpr int NS = 2 * D + 3;
+    double S[NS];
+#pragma unroll
     for (int j = 0; j < NS; ++j) S[j] = 0.0;
-    for (int s = 0; s < P.nslices; ++s) {
+#pragma unroll 2
+    for (int s = lane; s < P.nslices; s += L) {
         const double* in = P.FS + ((long long)(s * D + d) * NS) * NE + f;
+#pragma unroll
         for (int j = 0; j < NS; ++j) S[j] += in[(long long)j * NE];
     }
-    double Wf[5] = {S[0], S[1], D >= 2 ? S[2] : 0.0, D >= 3 ? S[3] : 0.0, 0.0};
-    Wf[D + 1] = S[D + 1];
+#pragma unroll
+    for (int j = 0; j < NS; ++j) S[j] = group_sum<L>(S[j], red);
+    double Wf[D + 2];
+#pragma unroll
+    for (int j = 0; j < D + 2; ++j) Wf[j] = S[j];
     if (P.has_accel) {
         // eqs. rhoubar, rhoEbar: (h/2) rho a and (h/2) (rho u).a, h/2 = dt/4,
         // with the face momentum just formed
+#pragma unroll
         for (int e = 0; e < D; ++e) Wf[1 + e] += 0.25 * P.dt * Wf[0] * P.accel[e];
+#pragma unroll
         for (int e = 0; e < D; ++e) Wf[D + 1] += 0.25 * P.dt * Wf[1 + e] * P.accel[e];
     }
-    Prim q = primitives(P, Wf);
-    if (q.bad) {
+    const Prim q = primitives(P, D, Wf);
+    if (q.bad) {  // the same for the whole group
         raise_error(P.err);
         return;
     }
     const double beta = 0.25 * P.dt * q.inv_tau_g;
     const double betab = beta * P.Pr;
     const double eta = beta * (P.Pr - 1.0);
-    const double A = maxwell_prefactor(P, q.rho, q.RT);
+    const double A = maxwell_prefactor(D, q.rho, q.RT);
     const double inv2RT = 0.5 / q.RT;
     const double hu2 = 0.5 * (q.u[0] * q.u[0] + q.u[1] * q.u[1] + q.u[2] * q.u[2]);
     const double cRT2 = 0.5 * P.c_int * q.RT;
 
     // separable discrete moments of the face Maxwellian: M[k][p] = sum_m w_m xi_m^p E_k(m)
-    double M[3][5];
+    double M[D][5];
     int off = 0;
-    for (int k = 0; k < 3; ++k) {
+#pragma unroll
+    for (int k = 0; k < D; ++k) {
+#pragma unroll
         for (int p = 0; p < 5; ++p) M[k][p] = 0.0;
-        if (k >= D) {
-            M[k][0] = 1.0;
-            continue;
-        }
-        for (int m = 0; m < P.nv[k]; ++m) {
-            double x = P.axis_xi[off + m];
+#pragma unroll 2
+        for (int m = lane; m < P.nv[k]; m += L) {
+            const double x = P.axis_xi[off + m];
             double e = P.axis_w[off + m] * exp(-(x - q.u[k]) * (x - q.u[k]) * inv2RT);
-            M[k][0] += e;
-            M[k][1] += e * x;
-            M[k][2] += e * x * x;
-            M[k][3] += e * x * x * x;
-            M[k][4] += e * x * x * x * x;
+#pragma unroll
+            for (int p = 0; p < 5; ++p) {
+                M[k][p] += e;
+                e *= x;
+            }
         }
         off += P.nv[k];
     }
-    auto prod0 = [&](int skip1, int skip2) {
-        double p = 1.0;
-        for (int k = 0; k < D; ++k)
-            if (k != skip1 && k != skip2) p *= M[k][0];
-        return p;
+#pragma unroll
+    for (int k = 0; k < D; ++k)
+#pragma unroll
+        for (int p = 0; p < 5; ++p) M[k][p] = group_sum<L>(M[k][p], red);
+    if (lane != 0) return;
+    // sum_i w_i xi_0^p0 xi_1^p1 xi_2^p2 g_eq / A, the exponents given per axis
+    auto mom = [&](const int (&p)[3]) __attribute__((always_inline)) {
+        double r = 1.0;
+#pragma unroll
+        for (int k = 0; k < D; ++k) {
+            // selects keep M in registers
+            const int pk = p[k];
+            r *= pk == 0 ? M[k][0] : (pk == 1 ? M[k][1] : (pk == 2 ? M[k][2] : (pk == 3 ? M[k][3] : M[k][4])));
+        }
+        return A * r;
+    };
+    auto power = [&](int a, int b = -1, int c = -1, int e = -1) __attribute__((always_inline)) {
+        int p[3];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) p[k] = (a == k) + (b == k) + (c == k) + (e == k);
+        return mom(p);
     };
     // equilibrium flux moments through a face with normal d
-    double E1 = A * M[d][1] * prod0(d, -1);
-    double E2[3];
-    for (int e = 0; e < D; ++e)
-        E2[e] = e == d ? A * M[d][2] * prod0(d, -1) : A * M[d][1] * M[e][1] * prod0(d, e);
-    double X3 = M[d][3] * prod0(d, -1);
-    for (int e = 0; e < D; ++e)
-        if (e != d) X3 += M[d][1] * M[e][2] * prod0(d, e);
-    X3 *= A;
-    double E3 = 0.5 * X3 + cRT2 * E1;
+    const double E1 = power(d);
+    double E2[D], X3 = 0.0;
+#pragma unroll
+    for (int e = 0; e < D; ++e) {
+        E2[e] = power(d, e);
+        X3 += power(d, e, e);
+    }
+    const double E3 = 0.5 * X3 + cRT2 * E1;
     double EZ = -hu2 * E1;
+#pragma unroll
     for (int e = 0; e < D; ++e) EZ += q.u[e] * E2[e];
 
     // phi at the face is affine in phi_bar (inversion of eq. phibar), so the
     // flux moments follow from the velocity sums of phi_bar and the
     // equilibrium moments above.
     const double ig = 1.0 / (1.0 + beta), ib = 1.0 / (1.0 + betab);
-    double Gm = (S[1 + d] + beta * E1) * ig;
-    double Gp[3];
+    double S1d = S[1];
+#pragma unroll
+    for (int e = 1; e < D; ++e) S1d = d == e ? S[1 + e] : S1d;
+    double Gm = (S1d + beta * E1) * ig;
+    double Gp[D];
+#pragma unroll
     for (int e = 0; e < D; ++e) Gp[e] = (S[D + 2 + e] + beta * E2[e]) * ig;
     double accE = 0.0;
     if (P.has_accel) {
@@ -1822,100 +1942,67 @@ __device__ void face_close_one(const Problem& P, long long idx) {
         // as ig c (a.xi - a.u) g_eq and b_f as ib [(dt/4) a.xi (g_f - g_eq)
         // + c (a.xi - a.u) b_eq], c = (h/2)/(R T); their flux moments need
         // third and fourth separable moments of the face Maxwellian.
-        auto mom = [&](const int* p) { return A * M[0][p[0]] * M[1][p[1]] * M[2][p[2]]; };
         const double c = 0.5 * P.dt * inv2RT;
         double au = 0.0, aE2 = 0.0;
+#pragma unroll
         for (int k = 0; k < D; ++k) {
             au += P.accel[k] * q.u[k];
             aE2 += P.accel[k] * E2[k];
         }
         Gm += ig * c * (aE2 - au * E1);
+#pragma unroll
         for (int e = 0; e < D; ++e) {
             double t3 = 0.0;  // sum_k a_k sum_i w_i xi_d xi_e xi_k g_eq
-            for (int k = 0; k < D; ++k) {
-                int p[3] = {0, 0, 0};
-                p[d] += 1;
-                p[e] += 1;
-                p[k] += 1;
-                t3 += P.accel[k] * mom(p);
-            }
+#pragma unroll
+            for (int k = 0; k < D; ++k) t3 += P.accel[k] * power(d, e, k);
             Gp[e] += ig * c * (t3 - au * E2[e]);
         }
         double aB2 = 0.0, aG = 0.0;  // sum_k a_k sum_i w_i xi_d xi_k b_eq; sum_k a_k (G_k - E2_k)
+#pragma unroll
         for (int k = 0; k < D; ++k) {
             double q4 = 0.0;
-            for (int m = 0; m < D; ++m) {
-                int p[3] = {0, 0, 0};
-                p[d] += 1;
-                p[k] += 1;
-                p[m] += 2;
-                q4 += mom(p);
-            }
+#pragma unroll
+            for (int m = 0; m < D; ++m) q4 += power(d, k, m, m);
             aB2 += P.accel[k] * (0.5 * q4 + cRT2 * E2[k]);
             aG += P.accel[k] * (Gp[k] - E2[k]);
         }
         accE = 0.25 * P.dt * aG + c * (aB2 - au * E3);
     }
     double ZG = -hu2 * Gm;
+#pragma unroll
     for (int e = 0; e < D; ++e) ZG += q.u[e] * Gp[e];
-    double Ge = (S[2 * D + 2] + betab * E3 + eta * (ZG - EZ) + accE) * ib;
+    const double Ge = (S[2 * D + 2] + betab * E3 + eta * (ZG - EZ) + accE) * ib;
 
     double* Go = P.G + (long long)d * (D + 2) * NE + f;
     Go[0] = Gm;
+#pragma unroll
     for (int e = 0; e < D; ++e) Go[(long long)(1 + e) * NE] = Gp[e];
     Go[(long long)(D + 1) * NE] = Ge;
 
     double* F = P.FP + (long long)d * NFP * NE + f;
-    F[PF_A * NE] = A;
-    F[PF_INV2RT * NE] = inv2RT;
-    F[PF_CRT2 * NE] = cRT2;
-    F[PF_IG * NE] = ig;
-    F[PF_IB * NE] = ib;
-    F[PF_EB * NE] = eta * ib;
-    F[PF_HU2 * NE] = hu2;
-    for (int e = 0; e < 3; ++e) F[(PF_U0 + e) * NE] = q.u[e];
+    F[PF_A * (long long)NE] = A;
+    F[PF_INV2RT * (long long)NE] = inv2RT;
+    F[PF_CRT2 * (long long)NE] = cRT2;
+    F[PF_IG * (long long)NE] = ig;
+    F[PF_IB * (long long)NE] = ib;
+    F[PF_EB * (long long)NE] = eta * ib;
+    F[PF_HU2 * (long long)NE] = hu2;
+#pragma unroll
+    for (int e = 0; e < 3; ++e) F[(PF_U0 + e) * (long long)NE] = q.u[e];
 }
 
-// ---------------------------------------------------------------------------
-// cell closure: W^{n+1} = W^n - dt sum_d (G_right - G_left)/dx_d; coefs at n+1
-// ---------------------------------------------------------------------------
-__device__ void cell_close_one(const Problem& P, long long c) {
-    if (c >= P.N) return;
-    const int D = P.D;
-    const long long N = P.N, NE = P.NE;
-    long long r = c;
-    int cc[3];
-    for (int e = 0; e < 3; ++e) {
-        cc[e] = (int)(r % P.n[e]);
-        r /= P.n[e];
+template <int D>
+__device__ __forceinline__ void face_close_lanes(const Problem& P, long long t, double* red) {
+    switch (P.close_lanes) {  // uniform per problem
+    case 1: face_close_group<D, 1>(P, t, red); break;
+    case 4: face_close_group<D, 4>(P, t, red); break;
+    case 16: face_close_group<D, 16>(P, t, red); break;
+    case 64: face_close_group<D, 64>(P, t, red); break;
+    default: face_close_group<D, 256>(P, t, red); break;
     }
-    long long fl = cc[0] + (long long)P.ne[0] * (cc[1] + (long long)P.ne[1] * cc[2]);
-    double Wn[5], W0[5];
-    for (int k = 0; k < D + 2; ++k) W0[k] = Wn[k] = P.W_in[k * N + c];
-    for (int d = 0; d < D; ++d) {
-        int rc[3] = {cc[0], cc[1], cc[2]};
-        rc[d] += 1;
-        if (P.bc[d] == 0 && rc[d] == P.n[d]) rc[d] = 0;
-        long long fr = rc[0] + (long long)P.ne[0] * (rc[1] + (long long)P.ne[1] * rc[2]);
-        const double* Gd = P.G + (long long)d * (D + 2) * NE;
-        for (int k = 0; k < D + 2; ++k)
-            Wn[k] -= P.dt * P.inv_dx[d] * (Gd[k * NE + fr] - Gd[k * NE + fl]);
-    }
-    if (P.has_accel) {
-        // source integrals at t_n (eqs. rhouupdate, rhoEupdate): rho a, (rho u).a
-        for (int e = 0; e < D; ++e) {
-            Wn[1 + e] += P.dt * W0[0] * P.accel[e];
-            Wn[D + 1] += P.dt * W0[1 + e] * P.accel[e];
-        }
-    }
-    for (int k = 0; k < D + 2; ++k) P.W_out[k * N + c] = Wn[k];
-    Prim q = primitives(P, Wn);
-    if (q.bad) raise_error(P.err);
-    write_cell_coefs(P, P.P_out, N, c, q);
 }
 
-
-// per-problem thread ranges for the batched per-face / per-cell launches
+// per-problem thread ranges of the batched per-face launch
 __device__ __forceinline__ int find_problem(const long long* offsets, int nprob, long long g) {
     int lo = 0, hi = nprob - 1;
     while (lo < hi) {

@@ -50,6 +50,7 @@ int resolve(const cdugks_space* sp, const cdugks_velocity* ve, const cdugks_para
 void resident_slots(int D, int storage, long long* R1, long long* R2);
 void velocity_tables(const Resolved& r, std::vector<double>& vel, std::vector<double>& axis);
 void dirichlet_tables(const Resolved& r, const std::vector<double>& vel, std::vector<double>& out);
+int close_lanes(const Resolved& r);
 void fill_problem(const Resolved& r, char* base, Problem& P);
 long long tail_rows(const Resolved& r, const std::vector<double>& vel, const double* u, const double* T,
                     std::vector<long long>& rows);

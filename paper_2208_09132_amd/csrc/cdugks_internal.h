@@ -85,6 +85,7 @@ struct Problem {
     const long long* rows;
     int recon;    // 0: slopes of slopes (Sec. 2.1), 1: single slope
     int tile;     // face-sum tile shape (index into tile_shape(D, .))
+    int close_lanes;  // threads per face of the face closure: 1, 4, 16, 64 or 256 (= WG)
     int has_accel;     // external acceleration present (a != 0)
     double accel[3];   // external acceleration a (eqs. gPDE, bPDE)
 };
@@ -119,7 +120,6 @@ int batched_face_blocks_per_cu(int maxd, int storage, bool accel);
 // on its own velocity grid; same cells and storage form.
 hipError_t launch_regrid(const Problem& Pn, const Problem& Po, hipStream_t s);
 hipError_t launch_face_close(const Problem& P, hipStream_t s);
-hipError_t launch_cell_close(const Problem& P, hipStream_t s);
 hipError_t launch_update(const Problem& P, hipStream_t s);
 hipError_t launch_moments(const Problem& P, const double* W, double* rho, double* u, double* T,
                           hipStream_t s);
@@ -140,7 +140,7 @@ hipError_t launch_face_sums_batched(const Problem* probs, const WorkItem* items,
 hipError_t launch_update_batched(const Problem* probs, const WorkItem* items, int nitems, int grid, int maxd,
                                  int storage, bool accel, int* queue, int* other, hipStream_t s);
 int batched_blocks_per_cu(int maxd, int storage, bool accel, bool update);
-hipError_t launch_face_close_batched(const Problem* probs, const long long* offsets, int nprob,
+hipError_t launch_face_close_batched(const Problem* probs, const long long* offsets, int nprob, int maxd,
                                      long long total, hipStream_t s);
 hipError_t launch_cell_close_batched(const Problem* probs, const long long* offsets, int nprob,
                                      long long total, hipStream_t s);

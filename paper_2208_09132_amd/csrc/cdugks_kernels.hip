@@ -10,7 +10,7 @@
 // Faces along d are indexed by the cell on their right on the extended grid
 // NE = prod_d (n_d + [outflow_d]).
 //
-// One step = four launches:
+// One step = three launches (four in a batch):
 //   face_sums  (tile kernel) : quarter-step field phi_bar_plus (eq. phibarplus),
 //                              Van Leer slopes (eq. VanLeer) and slopes of slopes,
 //                              face value at the characteristic foot (eq. relation),
@@ -19,9 +19,9 @@
 //   face_close (per face)    : face W (eqs. rhobar..rhoEbar), face equilibrium and
 //                              relaxation, inversion coefficients (eq. phibar), and
 //                              the flux moments in closed form
-//   cell_close (per cell)    : W^{n+1} from the flux moments (eqs. rhoupdate..
-//                              rhoEupdate, outward-flux sign), cell coefficients at n+1
-//   update     (streaming)   : stored face values, inversion (eq. phibar),
+//   update     (streaming)   : W^{n+1} from the flux moments (eqs. rhoupdate..
+//                              rhoEupdate, outward-flux sign) and the cell coefficients
+//                              at n+1 (a launch of its own in a batch); stored face values, inversion (eq. phibar),
 //                              microflux (eq. flux) and phi^{n+1} (eq. phiupdate)
 //
 // Face sums: one thread per cell of a 256-cell tile; the thread loops over
@@ -54,9 +54,9 @@ __global__ __launch_bounds__(WG) void k_init_cells(Problem P, const double* rho,
     // rho E = rho (u^2/2 + c_v T), c_v = (3+K)R/2 = R/(gamma-1)
     Wv[D + 1] = rho[c] * (0.5 * u2 + P.R * T[c] / (P.gamma - 1.0));
     for (int k = 0; k < D + 2; ++k) const_cast<double*>(P.W_in)[k * N + c] = Wv[k];
-    Prim q = primitives(P, Wv);
+    Prim q = primitives(P, P.D, Wv);
     if (q.bad) raise_error(P.err);
-    write_cell_coefs(P, const_cast<double*>(P.P_in), N, c, q);
+    store_coef(const_cast<double*>(P.P_in), N, c, cell_coefs(P, P.D, q));
 }
 
 template <typename ST>
@@ -122,9 +122,9 @@ __global__ __launch_bounds__(WG) void k_cell_coefs(Problem P) {
     if (c >= P.N) return;
     double Wv[5];
     for (int k = 0; k < P.D + 2; ++k) Wv[k] = P.W_in[k * P.N + c];
-    const Prim q = primitives(P, Wv);
+    const Prim q = primitives(P, P.D, Wv);
     if (q.bad) raise_error(P.err);
-    write_cell_coefs(P, const_cast<double*>(P.P_in), P.N, c, q);
+    store_coef(const_cast<double*>(P.P_in), P.N, c, cell_coefs(P, P.D, q));
 }
 
 template <int D, typename ST>
@@ -210,31 +210,43 @@ __global__ __launch_bounds__(WG) void k_update_batched(const Problem* probs, con
         const WorkItem it = load_uniform(items + w);
         const Problem P = load_uniform(probs + it.prob);
         const long long c = (long long)it.tile * WG + threadIdx.x;
-        if (P.D == 1) UpdateKernel<1, ST, ACC>::run(P, c, it.slice, it.nslices);
-        else if (MAXD >= 2 && P.D == 2) UpdateKernel<MAXD >= 2 ? 2 : 1, ST, ACC>::run(P, c, it.slice, it.nslices);
-        else if (MAXD >= 3) UpdateKernel<MAXD >= 3 ? 3 : 1, ST, ACC>::run(P, c, it.slice, it.nslices);
+        if (P.D == 1) UpdateKernel<1, ST, ACC, 0, false>::run(P, c, it.slice, it.nslices);
+        else if (MAXD >= 2 && P.D == 2) UpdateKernel<MAXD >= 2 ? 2 : 1, ST, ACC, 0, false>::run(P, c, it.slice, it.nslices);
+        else if (MAXD >= 3) UpdateKernel<MAXD >= 3 ? 3 : 1, ST, ACC, 0, false>::run(P, c, it.slice, it.nslices);
     }
 }
 
+template <int D>
 __global__ __launch_bounds__(WG) void k_face_close(Problem P) {
-    face_close_one(P, (long long)blockIdx.x * WG + threadIdx.x);
+    __shared__ double red[WG / 64];
+    face_close_lanes<D>(P, (long long)blockIdx.x * WG + threadIdx.x, red);
 }
-
-__global__ __launch_bounds__(WG) void k_cell_close(Problem P) {
-    cell_close_one(P, (long long)blockIdx.x * WG + threadIdx.x);
-}
-
 
 // Batched closures: every problem's range of threads starts on a workgroup
 // boundary (offsets in threads, multiples of WG), so a workgroup serves one
 // problem, found once per workgroup (its descriptor then read at one address
-// by every lane); threads past the problem's faces (cells) return.
+// by every lane); threads past the problem's faces (cells) return.  MAXD is
+// the largest dimension of the batch.
+template <int MAXD>
 __global__ __launch_bounds__(WG) void k_face_close_batched(const Problem* probs, const long long* offsets,
                                                            int nprob, long long total) {
+    __shared__ double red[WG / 64];
     const long long g0 = (long long)blockIdx.x * WG;
     if (g0 >= total) return;
     const int p = __builtin_amdgcn_readfirstlane(find_problem(offsets, nprob, g0));
-    face_close_one(probs[p], g0 - offsets[p] + threadIdx.x);  // by reference: no private copy
+    const Problem& P = probs[p];  // by reference: no private copy
+    const long long t = g0 - offsets[p] + threadIdx.x;
+    if (P.D == 1) face_close_lanes<1>(P, t, red);
+    else if (MAXD >= 2 && P.D == 2) face_close_lanes<MAXD >= 2 ? 2 : 1>(P, t, red);
+    else if (MAXD >= 3) face_close_lanes<MAXD >= 3 ? 3 : 1>(P, t, red);
+}
+
+template <int D>
+__device__ __forceinline__ void cell_close_one(const Problem& P, long long c) {
+    if (c >= P.N) return;
+    unsigned fl[D], fr[D];
+    cell_faces<D>(P, (unsigned)c, fl, fr);
+    cell_close<D>(P, c, fl, fr, true);
 }
 
 __global__ __launch_bounds__(WG) void k_cell_close_batched(const Problem* probs, const long long* offsets,
@@ -242,7 +254,11 @@ __global__ __launch_bounds__(WG) void k_cell_close_batched(const Problem* probs,
     const long long g0 = (long long)blockIdx.x * WG;
     if (g0 >= total) return;
     const int p = __builtin_amdgcn_readfirstlane(find_problem(offsets, nprob, g0));
-    cell_close_one(probs[p], g0 - offsets[p] + threadIdx.x);
+    const Problem& P = probs[p];
+    const long long c = g0 - offsets[p] + threadIdx.x;
+    if (P.D == 1) cell_close_one<1>(P, c);
+    else if (P.D == 2) cell_close_one<2>(P, c);
+    else cell_close_one<3>(P, c);
 }
 
 // ---------------------------------------------------------------------------
@@ -388,12 +404,10 @@ int tile_blocks_per_cu(int D, int storage, bool update) {
 }
 
 hipError_t launch_face_close(const Problem& P, hipStream_t s) {
-    hipLaunchKernelGGL(k_face_close, dim3(blocks_for(P.NE * P.D)), dim3(WG), 0, s, P);
-    return hipGetLastError();
-}
-
-hipError_t launch_cell_close(const Problem& P, hipStream_t s) {
-    hipLaunchKernelGGL(k_cell_close, dim3(blocks_for(P.N)), dim3(WG), 0, s, P);
+    const dim3 grid(blocks_for(P.NE * P.D * P.close_lanes));
+    if (P.D == 1) hipLaunchKernelGGL(k_face_close<1>, grid, dim3(WG), 0, s, P);
+    else if (P.D == 2) hipLaunchKernelGGL(k_face_close<2>, grid, dim3(WG), 0, s, P);
+    else hipLaunchKernelGGL(k_face_close<3>, grid, dim3(WG), 0, s, P);
     return hipGetLastError();
 }
 
@@ -468,11 +482,13 @@ int batched_blocks_per_cu(int maxd, int storage, bool accel, bool update) {
     return n;
 }
 
-hipError_t launch_face_close_batched(const Problem* probs, const long long* offsets, int nprob,
+hipError_t launch_face_close_batched(const Problem* probs, const long long* offsets, int nprob, int maxd,
                                      long long total, hipStream_t s) {
     if (total <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_face_close_batched, dim3(blocks_for(total)), dim3(WG), 0, s, probs, offsets, nprob,
-                       total);
+    const dim3 grid(blocks_for(total));
+    if (maxd == 1) hipLaunchKernelGGL(k_face_close_batched<1>, grid, dim3(WG), 0, s, probs, offsets, nprob, total);
+    else if (maxd == 2) hipLaunchKernelGGL(k_face_close_batched<2>, grid, dim3(WG), 0, s, probs, offsets, nprob, total);
+    else hipLaunchKernelGGL(k_face_close_batched<3>, grid, dim3(WG), 0, s, probs, offsets, nprob, total);
     return hipGetLastError();
 }
 hipError_t launch_cell_close_batched(const Problem* probs, const long long* offsets, int nprob,
@@ -482,5 +498,4 @@ hipError_t launch_cell_close_batched(const Problem* probs, const long long* offs
                        total);
     return hipGetLastError();
 }
-
 }  // namespace cdg

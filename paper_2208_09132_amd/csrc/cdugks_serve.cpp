@@ -138,6 +138,7 @@ struct cdugks_batch {
     long long* d_face_off = nullptr;
     long long* d_cell_off = nullptr;
     long long face_total = 0, cell_total = 0;
+    int maxd = 1;  // largest dimension
     std::vector<StorageClass> classes;
     hipGraphExec_t graph[2] = {nullptr, nullptr};
     std::vector<hipStream_t> others;  // streams of members other than the batch stream
@@ -154,7 +155,8 @@ hipError_t enqueue_batch_step(cdugks_batch* b, int phase) {
         if ((e = launch_face_sums_batched(probs, c.items_fs, c.n_fs, c.grid_fs, c.maxd, c.storage, c.dirichlet,
                                           c.single_slope, c.accel, c.queue, c.queue + 1, b->stream)) != hipSuccess)
             return e;
-    if ((e = launch_face_close_batched(probs, b->d_face_off, np, b->face_total, b->stream)) != hipSuccess) return e;
+    if ((e = launch_face_close_batched(probs, b->d_face_off, np, b->maxd, b->face_total, b->stream)) != hipSuccess)
+        return e;
     if ((e = launch_cell_close_batched(probs, b->d_cell_off, np, b->cell_total, b->stream)) != hipSuccess) return e;
     for (auto& c : b->classes)
         if ((e = launch_update_batched(probs, c.items_up, c.n_up, c.grid_up, c.maxd, c.storage, c.accel,
@@ -252,10 +254,11 @@ int batch_build(cdugks_ctx* const* ctxs, int count, int chunk_steps, cdugks_batc
             for (int d = 0; d < 3; ++d) P.tiles1[d] = batched_tiles(c->r, d);
             probs[p].push_back(P);
         }
+        b->maxd = std::max(b->maxd, c->r.D);
         face_off[j] = ft;
         cell_off[j] = ct;
         // each problem's closure threads start on a workgroup boundary
-        ft += (c->r.NE * c->r.D + WG - 1) / WG * WG;
+        ft += (c->r.NE * c->r.D * c->P.close_lanes + WG - 1) / WG * WG;
         ct += (c->r.N + WG - 1) / WG * WG;
     }
     b->face_total = ft;
