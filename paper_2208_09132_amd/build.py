@@ -18,6 +18,7 @@ UNITS = [("cdugks_kernels.hip", "cdugks_kernels", []),
          ("cdugks_batched.hip", "cdugks_batched", []),
          ("cdugks_api.cpp", "cdugks_api", []),
          ("cdugks_serve.cpp", "cdugks_serve", []),
+         ("cdugks_pool.cpp", "cdugks_pool", []),
          ("cdugks_vgrid.cpp", "cdugks_vgrid", [])]
 JOBS = int(os.environ.get("CDUGKS_BUILD_JOBS", "8"))
 ARCH = os.environ.get("CDUGKS_ARCH", "gfx950")

@@ -134,6 +134,8 @@ struct cdugks_batch {
     int chunk = 2;
     int phase = 0;  // 0: every context at the parity it had when batched
     char* dev = nullptr;
+    int device = 0;         // where the tables live
+    size_t dev_bytes = 0;
     Problem* d_probs[2] = {nullptr, nullptr};
     long long* d_face_off = nullptr;
     long long* d_cell_off = nullptr;
@@ -184,10 +186,11 @@ hipError_t capture_batch(cdugks_batch* b, int phase, hipGraphExec_t* exec) {
 
 void batch_free(cdugks_batch* b) {
     if (!b) return;
-    if (b->stream) (void)hipStreamSynchronize(b->stream);
+    const bool idle = !b->stream || hipStreamSynchronize(b->stream) == hipSuccess;
     for (int k = 0; k < 2; ++k)
         if (b->graph[k]) (void)hipGraphExecDestroy(b->graph[k]);
-    if (b->dev) (void)hipFree(b->dev);
+    if (b->dev && idle) pool_give(b->device, b->dev, b->dev_bytes);
+    else if (b->dev) (void)hipFree(b->dev);
     if (b->ev) (void)hipEventDestroy(b->ev);
     for (auto* c : b->ctxs) c->in_batch = false;
     delete b;
@@ -322,7 +325,10 @@ int batch_build(cdugks_ctx* const* ctxs, int count, int chunk_steps, cdugks_batc
         o_up[s] = reserve(sizeof(WorkItem) * std::max<size_t>(1, up[s].size()));
         o_q[s] = reserve(2 * sizeof(int));  // zero in the uploaded image
     }
-    hipError_t e = hipMalloc(&b->dev, bytes);
+    void* block = nullptr;
+    hipError_t e = hipGetDevice(&b->device);
+    if (e == hipSuccess) e = pool_take(b->device, bytes, SIZE_MAX, &block, &b->dev_bytes);
+    b->dev = (char*)block;
     if (e != hipSuccess) {
         (void)hipGetLastError();
         delete b;
@@ -486,8 +492,16 @@ void server_loop(cdugks_server* s) {
         }
         for (Request* r : admit) {
             r->t_admit = now_s();
-            int rc = cdugks_init(&r->sp, &r->ve, &r->pa, r->rho.data(), r->u.data(), r->T.data(), s->stream,
-                                 nullptr, 0, &r->ctx);
+            // idle blocks count against the budget, and a reused block may be
+            // larger than the request only by what the budget still allows
+            size_t room = 0;
+            {
+                std::lock_guard<std::mutex> lock(s->mu);
+                room = s->budget - s->used;
+            }
+            pool_trim(s->device, room);
+            int rc = init_context(&r->sp, &r->ve, &r->pa, r->rho.data(), r->u.data(), r->T.data(), s->stream,
+                                  nullptr, 0, r->bytes + room, &r->ctx);
             std::lock_guard<std::mutex> lock(s->mu);
             if (rc) {
                 r->status = rc;
@@ -497,6 +511,8 @@ void server_loop(cdugks_server* s) {
                 s->cv.notify_all();
                 continue;
             }
+            s->used += r->ctx->own_bytes - r->bytes;
+            r->bytes = r->ctx->own_bytes;
             r->remaining = r->nsteps;
             s->active.push_back(r);
             dirty = true;
@@ -620,9 +636,11 @@ int cdugks_server_create(size_t hbm_budget, int max_active, int chunk_steps, voi
         }
         s->own_stream = true;
     }
+    pool_user(s->device, 1);
     try {
         s->worker = std::thread(server_loop, s);
     } catch (...) {
+        pool_user(s->device, -1);
         if (s->own_stream) (void)hipStreamDestroy(s->stream);
         delete s;
         return fail(CDUGKS_ERR_UNKNOWN, "could not start the server thread");
@@ -708,6 +726,7 @@ void cdugks_server_destroy(cdugks_server* s) {
     s->cv.notify_all();
     if (s->worker.joinable()) s->worker.join();
     for (auto& kv : s->live) delete kv.second;  // queued, failed or uncollected
+    pool_user(s->device, -1);
     if (s->own_stream) (void)hipStreamDestroy(s->stream);
     delete s;
 }
