@@ -462,18 +462,17 @@ void dirichlet_tables(const Resolved& r, const std::vector<double>& vel, std::ve
     }
 }
 
-// Threads per face of the face closure.  One is enough where the faces alone
-// give every SIMD four waves (256 CUs x 4 SIMDs x 4 x 64 threads: the 3-D
-// workload's 7.9e5 faces take 0.11 ms); otherwise the smallest group that
-// reaches that many threads, but none whose threads would get fewer than two
-// of a face's nodes or slices.
-int close_lanes(const Resolved& r) {
-    constexpr long long FILL = 256 * 4 * 4 * 64;
-    const long long faces = r.NE * r.D;
-    const int serial = std::max(r.nslices, std::max(r.nv[0], std::max(r.nv[1], r.nv[2])));
-    if (faces >= FILL) return 1;
-    int l = 4;
-    while (l < WG && faces * l < FILL && 8 * l <= serial) l *= 4;
+// Threads per face of the face closure (speed only), of a launch that closes
+// `faces` faces.  One where those fill the device, unless a face's nodes are
+// so many that its thread would outlast the launch; else groups that share a
+// face's nodes: larger ones for longer axes, as long as two workgroups per CU
+// hold them all.
+int close_lanes(const Resolved& r, long long faces) {
+    constexpr long long MANY_FACES = 1 << 16, ROOM = 256 * 2 * WG;
+    const int nodes = (r.D >= 1 ? r.nv[0] : 0) + (r.D >= 2 ? r.nv[1] : 0) + (r.D >= 3 ? r.nv[2] : 0);
+    if (faces >= MANY_FACES && nodes <= 256) return 1;
+    int l = 16;
+    while (l < WG && nodes > 2 * l && 4 * l * faces <= ROOM) l *= 4;
     return l;
 }
 
@@ -525,7 +524,7 @@ void fill_problem(const Resolved& r, char* base, Problem& P) {
     P.rows = r.storage == CDUGKS_STORE_F32_BF16TAIL ? (const long long*)(base + r.off_rows) : nullptr;
     P.recon = r.recon;
     P.tile = r.tile;
-    P.close_lanes = close_lanes(r);
+    P.close_lanes = close_lanes(r, r.NE * r.D);
     P.has_accel = r.has_accel ? 1 : 0;
     for (int d = 0; d < 3; ++d) P.accel[d] = r.accel[d];
 }

@@ -263,9 +263,6 @@ struct Prim {
     bool bad;
 };
 
-// mu = mu_ref (T/T_ref)^omega; the hard-sphere exponent 1/2 (the usual one)
-// takes the square root, which is exact to half an ulp and a fraction of the
-// general power's instructions.
 __device__ __forceinline__ Prim primitives(const Problem& P, int D, const double* Wv) {
     Prim q;
     q.rho = Wv[0];
@@ -278,8 +275,7 @@ __device__ __forceinline__ Prim primitives(const Problem& P, int D, const double
     double T = (P.gamma - 1.0) / P.R * (E - 0.5 * u2);
     q.RT = P.R * T;
     if (P.relax == 0) {
-        const double t = T / P.T_ref;
-        const double mu = P.mu_ref * (P.omega == 0.5 ? sqrt(t) : pow(t, P.omega));
+        double mu = P.mu_ref * pow(T / P.T_ref, P.omega);
         q.inv_tau_g = q.rho * q.RT / mu;
     } else {
         q.inv_tau_g = P.tau_inv;
@@ -1786,66 +1782,22 @@ __device__ __forceinline__ T load_uniform(const T* p) {
 }
 
 // ---------------------------------------------------------------------------
-// face closure: W_f, coefficients, flux moments; L threads per (d, face)
+// face closure: W_f, coefficients, flux moments
 // ---------------------------------------------------------------------------
-// The serial part of a face is the sum over the velocity slices' partial sums
-// and, per velocity axis, an exponential and five products per node.  L
-// neighbouring threads (a power of 4 up to the workgroup) share both: thread l
-// takes slices and nodes l, l + L, ..., and a butterfly over the group leaves
-// the same sums in every thread.  L is fixed per problem (close_lanes on the
-// host), so a face's sums are formed in the same order in every launch form.
-// With one thread per face a step of the 128 x 16385 sine wave spent 2.86 ms
-// of its 3.31 ms here, at 1/500 of the device's threads.
-template <int L>
-__device__ __forceinline__ double group_sum(double v, double* red) {
-    constexpr int W = L < 64 ? L : 64;
+// Whether face f (extended-grid index) with normal d lies in the grid.
+template <int D>
+__device__ __forceinline__ bool face_in_grid(const Problem& P, int d, unsigned f) {
+    const unsigned ne0 = P.ne[0], ne1 = P.ne[1];
+    const unsigned cc[3] = {f % ne0, D >= 2 ? (f / ne0) % ne1 : 0, D >= 3 ? f / (ne0 * ne1) : 0};
+    bool in = true;
 #pragma unroll
-    for (int m = 1; m < W; m <<= 1) v += __shfl_xor(v, m, 64);
-    if constexpr (L > 64) {
-        // across the waves of the workgroup, in wave order
-        const int w = threadIdx.x >> 6;
-        if ((threadIdx.x & 63) == 0) red[w] = v;
-        __syncthreads();
-        v = red[0];
-#pragma unroll
-        for (int k = 1; k < L / 64; ++k) v += red[k];
-        __syncthreads();
-    }
-    return v;
+    for (int e = 0; e < D; ++e) in &= cc[e] < (unsigned)P.n[e] || (e == d && P.bc[e] != 0);
+    return in;
 }
 
-// thread t of the problem's closure threads; with L > 64 the group is the
-// workgroup, whose threads all call this together
-template <int D, int L>
-__device__ __forceinline__ void face_close_group(const Problem& P, long long t, double* red) {
-    const unsigned NE = (unsigned)P.NE;
-    const long long idx = t / L;
-    const int lane = (int)(threadIdx.x % L);
-    if (idx >= (long long)NE * D) return;
-    const int d = (int)(idx / NE);
-    const unsigned f = (unsigned)(idx - (long long)d * NE);
-    {
-        const unsigned ne0 = P.ne[0], ne1 = P.ne[1];
-        const unsigned cc[3] = {f % ne0, (f / ne0) % ne1, f / (ne0 * ne1)};
-#pragma unroll
-        for (int e = 0; e < D; ++e)
-            if (e != d && cc[e] >= (unsigned)P.n[e]) return;
-        const unsigned cd = d == 0 ? cc[0] : (d == 1 ? cc[1] : cc[2]);
-        if (P.bc[d] == 0 && cd >= (unsigned)P.n[d]) return;
-    }
-
-    constexpr int NS = 2 * D + 3;
-    double S[NS];
-#pragma unroll
-    for (int j = 0; j < NS; ++j) S[j] = 0.0;
-#pragma unroll 2
-    for (int s = lane; s < P.nslices; s += L) {
-        const double* in = P.FS + ((long long)(s * D + d) * NS) * NE + f;
-#pragma unroll
-        for (int j = 0; j < NS; ++j) S[j] += in[(long long)j * NE];
-    }
-#pragma unroll
-    for (int j = 0; j < NS; ++j) S[j] = group_sum<L>(S[j], red);
+// W_f from the face's velocity sums S, and its primitives.
+template <int D>
+__device__ __forceinline__ Prim face_primitives(const Problem& P, const double (&S)[2 * D + 3]) {
     double Wf[D + 2];
 #pragma unroll
     for (int j = 0; j < D + 2; ++j) Wf[j] = S[j];
@@ -1857,11 +1809,15 @@ __device__ __forceinline__ void face_close_group(const Problem& P, long long t, 
 #pragma unroll
         for (int e = 0; e < D; ++e) Wf[D + 1] += 0.25 * P.dt * Wf[1 + e] * P.accel[e];
     }
-    const Prim q = primitives(P, D, Wf);
-    if (q.bad) {  // the same for the whole group
-        raise_error(P.err);
-        return;
-    }
+    return primitives(P, D, Wf);
+}
+
+// The face's coefficients and flux moments from its sums S and the separable
+// discrete moments of its Maxwellian, M[k][p] = sum_m w_m xi_m^p E_k(m).
+template <int D>
+__device__ __forceinline__ void face_finish(const Problem& P, int dn, unsigned f, const double (&S)[2 * D + 3],
+                                            const Prim& q, const double (&M)[D][5]) {
+    const long long NE = P.NE;
     const double beta = 0.25 * P.dt * q.inv_tau_g;
     const double betab = beta * P.Pr;
     const double eta = beta * (P.Pr - 1.0);
@@ -1869,136 +1825,350 @@ __device__ __forceinline__ void face_close_group(const Problem& P, long long t, 
     const double inv2RT = 0.5 / q.RT;
     const double hu2 = 0.5 * (q.u[0] * q.u[0] + q.u[1] * q.u[1] + q.u[2] * q.u[2]);
     const double cRT2 = 0.5 * P.c_int * q.RT;
+    double* const Go = P.G + (long long)dn * (D + 2) * NE + f;
+    // one body per normal, so every index of M and S is a constant
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+        if (d != dn) continue;
+        auto prod0 = [&](int skip1, int skip2) __attribute__((always_inline)) {
+            double p = 1.0;
+#pragma unroll
+            for (int k = 0; k < D; ++k)
+                if (k != skip1 && k != skip2) p *= M[k][0];
+            return p;
+        };
+        // equilibrium flux moments through a face with normal d
+        double E1 = A * M[d][1] * prod0(d, -1);
+        double E2[D];
+#pragma unroll
+        for (int e = 0; e < D; ++e)
+            E2[e] = e == d ? A * M[d][2] * prod0(d, -1) : A * M[d][1] * M[e][1] * prod0(d, e);
+        double X3 = M[d][3] * prod0(d, -1);
+#pragma unroll
+        for (int e = 0; e < D; ++e)
+            if (e != d) X3 += M[d][1] * M[e][2] * prod0(d, e);
+        X3 *= A;
+        double E3 = 0.5 * X3 + cRT2 * E1;
+        double EZ = -hu2 * E1;
+#pragma unroll
+        for (int e = 0; e < D; ++e) EZ += q.u[e] * E2[e];
 
-    // separable discrete moments of the face Maxwellian: M[k][p] = sum_m w_m xi_m^p E_k(m)
+        // phi at the face is affine in phi_bar (inversion of eq. phibar), so
+        // the flux moments follow from the velocity sums of phi_bar and the
+        // equilibrium moments above.
+        const double ig = 1.0 / (1.0 + beta), ib = 1.0 / (1.0 + betab);
+        double Gm = (S[1 + d] + beta * E1) * ig;
+        double Gp[D];
+#pragma unroll
+        for (int e = 0; e < D; ++e) Gp[e] = (S[D + 2 + e] + beta * E2[e]) * ig;
+        double accE = 0.0;
+        if (P.has_accel) {
+            // The acceleration's (h/2) S terms at the face (eqs. gsource,
+            // bsource with the velocity derivative on the equilibrium) enter
+            // g_f as ig c (a.xi - a.u) g_eq and b_f as ib [(dt/4) a.xi (g_f -
+            // g_eq) + c (a.xi - a.u) b_eq], c = (h/2)/(R T); their flux
+            // moments need third and fourth separable moments of the face
+            // Maxwellian.
+            auto mom = [&](const int (&p)[3]) __attribute__((always_inline)) {
+                double r = A * M[0][p[0]];
+#pragma unroll
+                for (int k = 1; k < D; ++k) r *= M[k][p[k]];
+                return r;
+            };
+            const double c = 0.5 * P.dt * inv2RT;
+            double au = 0.0, aE2 = 0.0;
+#pragma unroll
+            for (int k = 0; k < D; ++k) {
+                au += P.accel[k] * q.u[k];
+                aE2 += P.accel[k] * E2[k];
+            }
+            Gm += ig * c * (aE2 - au * E1);
+#pragma unroll
+            for (int e = 0; e < D; ++e) {
+                double t3 = 0.0;  // sum_k a_k sum_i w_i xi_d xi_e xi_k g_eq
+#pragma unroll
+                for (int k = 0; k < D; ++k) {
+                    int p[3] = {0, 0, 0};
+                    p[d] += 1;
+                    p[e] += 1;
+                    p[k] += 1;
+                    t3 += P.accel[k] * mom(p);
+                }
+                Gp[e] += ig * c * (t3 - au * E2[e]);
+            }
+            double aB2 = 0.0, aG = 0.0;  // sum_k a_k sum_i w_i xi_d xi_k b_eq; sum_k a_k (G_k - E2_k)
+#pragma unroll
+            for (int k = 0; k < D; ++k) {
+                double q4 = 0.0;
+#pragma unroll
+                for (int m = 0; m < D; ++m) {
+                    int p[3] = {0, 0, 0};
+                    p[d] += 1;
+                    p[k] += 1;
+                    p[m] += 2;
+                    q4 += mom(p);
+                }
+                aB2 += P.accel[k] * (0.5 * q4 + cRT2 * E2[k]);
+                aG += P.accel[k] * (Gp[k] - E2[k]);
+            }
+            accE = 0.25 * P.dt * aG + c * (aB2 - au * E3);
+        }
+        double ZG = -hu2 * Gm;
+#pragma unroll
+        for (int e = 0; e < D; ++e) ZG += q.u[e] * Gp[e];
+        double Ge = (S[2 * D + 2] + betab * E3 + eta * (ZG - EZ) + accE) * ib;
+
+        Go[0] = Gm;
+#pragma unroll
+        for (int e = 0; e < D; ++e) Go[(long long)(1 + e) * NE] = Gp[e];
+        Go[(long long)(D + 1) * NE] = Ge;
+        double* F = P.FP + (long long)d * NFP * NE + f;
+        F[PF_A * NE] = A;
+        F[PF_INV2RT * NE] = inv2RT;
+        F[PF_CRT2 * NE] = cRT2;
+        F[PF_IG * NE] = ig;
+        F[PF_IB * NE] = ib;
+        F[PF_EB * NE] = eta * ib;
+        F[PF_HU2 * NE] = hu2;
+#pragma unroll
+        for (int e = 0; e < 3; ++e) F[(PF_U0 + e) * NE] = q.u[e];
+    }
+}
+
+// One thread per face: t counts (normal, face).
+template <int D>
+__device__ __forceinline__ void face_close_one(const Problem& P, long long t) {
+    const unsigned NE = (unsigned)P.NE;
+    if (t >= (long long)NE * D) return;
+    const int d = (int)(t / NE);
+    const unsigned f = (unsigned)(t - (long long)d * NE);
+    if (!face_in_grid<D>(P, d, f)) return;
+    constexpr int NS = 2 * D + 3;
+    double S[NS];
+#pragma unroll
+    for (int j = 0; j < NS; ++j) S[j] = 0.0;
+#pragma unroll 2
+    for (int s = 0; s < P.nslices; ++s) {
+        const double* in = P.FS + ((long long)(s * D + d) * NS) * NE + f;
+#pragma unroll
+        for (int j = 0; j < NS; ++j) S[j] += in[(long long)j * NE];
+    }
+    const Prim q = face_primitives<D>(P, S);
+    if (q.bad) {
+        raise_error(P.err);
+        return;
+    }
+    const double inv2RT = 0.5 / q.RT;
     double M[D][5];
     int off = 0;
 #pragma unroll
     for (int k = 0; k < D; ++k) {
 #pragma unroll
         for (int p = 0; p < 5; ++p) M[k][p] = 0.0;
-#pragma unroll 2
-        for (int m = lane; m < P.nv[k]; m += L) {
-            const double x = P.axis_xi[off + m];
+#pragma unroll 4
+        for (int m = 0; m < P.nv[k]; ++m) {
+            double x = P.axis_xi[off + m];
             double e = P.axis_w[off + m] * exp(-(x - q.u[k]) * (x - q.u[k]) * inv2RT);
-#pragma unroll
-            for (int p = 0; p < 5; ++p) {
-                M[k][p] += e;
-                e *= x;
-            }
+            M[k][0] += e;
+            M[k][1] += e * x;
+            M[k][2] += e * x * x;
+            M[k][3] += e * x * x * x;
+            M[k][4] += e * x * x * x * x;
         }
         off += P.nv[k];
     }
-#pragma unroll
-    for (int k = 0; k < D; ++k)
-#pragma unroll
-        for (int p = 0; p < 5; ++p) M[k][p] = group_sum<L>(M[k][p], red);
-    if (lane != 0) return;
-    // sum_i w_i xi_0^p0 xi_1^p1 xi_2^p2 g_eq / A, the exponents given per axis
-    auto mom = [&](const int (&p)[3]) __attribute__((always_inline)) {
-        double r = 1.0;
-#pragma unroll
-        for (int k = 0; k < D; ++k) {
-            // selects keep M in registers
-            const int pk = p[k];
-            r *= pk == 0 ? M[k][0] : (pk == 1 ? M[k][1] : (pk == 2 ? M[k][2] : (pk == 3 ? M[k][3] : M[k][4])));
-        }
-        return A * r;
-    };
-    auto power = [&](int a, int b = -1, int c = -1, int e = -1) __attribute__((always_inline)) {
-        int p[3];
-#pragma unroll
-        for (int k = 0; k < 3; ++k) p[k] = (a == k) + (b == k) + (c == k) + (e == k);
-        return mom(p);
-    };
-    // equilibrium flux moments through a face with normal d
-    const double E1 = power(d);
-    double E2[D], X3 = 0.0;
-#pragma unroll
-    for (int e = 0; e < D; ++e) {
-        E2[e] = power(d, e);
-        X3 += power(d, e, e);
-    }
-    const double E3 = 0.5 * X3 + cRT2 * E1;
-    double EZ = -hu2 * E1;
-#pragma unroll
-    for (int e = 0; e < D; ++e) EZ += q.u[e] * E2[e];
-
-    // phi at the face is affine in phi_bar (inversion of eq. phibar), so the
-    // flux moments follow from the velocity sums of phi_bar and the
-    // equilibrium moments above.
-    const double ig = 1.0 / (1.0 + beta), ib = 1.0 / (1.0 + betab);
-    double S1d = S[1];
-#pragma unroll
-    for (int e = 1; e < D; ++e) S1d = d == e ? S[1 + e] : S1d;
-    double Gm = (S1d + beta * E1) * ig;
-    double Gp[D];
-#pragma unroll
-    for (int e = 0; e < D; ++e) Gp[e] = (S[D + 2 + e] + beta * E2[e]) * ig;
-    double accE = 0.0;
-    if (P.has_accel) {
-        // The acceleration's (h/2) S terms at the face (eqs. gsource,
-        // bsource with the velocity derivative on the equilibrium) enter g_f
-        // as ig c (a.xi - a.u) g_eq and b_f as ib [(dt/4) a.xi (g_f - g_eq)
-        // + c (a.xi - a.u) b_eq], c = (h/2)/(R T); their flux moments need
-        // third and fourth separable moments of the face Maxwellian.
-        const double c = 0.5 * P.dt * inv2RT;
-        double au = 0.0, aE2 = 0.0;
-#pragma unroll
-        for (int k = 0; k < D; ++k) {
-            au += P.accel[k] * q.u[k];
-            aE2 += P.accel[k] * E2[k];
-        }
-        Gm += ig * c * (aE2 - au * E1);
-#pragma unroll
-        for (int e = 0; e < D; ++e) {
-            double t3 = 0.0;  // sum_k a_k sum_i w_i xi_d xi_e xi_k g_eq
-#pragma unroll
-            for (int k = 0; k < D; ++k) t3 += P.accel[k] * power(d, e, k);
-            Gp[e] += ig * c * (t3 - au * E2[e]);
-        }
-        double aB2 = 0.0, aG = 0.0;  // sum_k a_k sum_i w_i xi_d xi_k b_eq; sum_k a_k (G_k - E2_k)
-#pragma unroll
-        for (int k = 0; k < D; ++k) {
-            double q4 = 0.0;
-#pragma unroll
-            for (int m = 0; m < D; ++m) q4 += power(d, k, m, m);
-            aB2 += P.accel[k] * (0.5 * q4 + cRT2 * E2[k]);
-            aG += P.accel[k] * (Gp[k] - E2[k]);
-        }
-        accE = 0.25 * P.dt * aG + c * (aB2 - au * E3);
-    }
-    double ZG = -hu2 * Gm;
-#pragma unroll
-    for (int e = 0; e < D; ++e) ZG += q.u[e] * Gp[e];
-    const double Ge = (S[2 * D + 2] + betab * E3 + eta * (ZG - EZ) + accE) * ib;
-
-    double* Go = P.G + (long long)d * (D + 2) * NE + f;
-    Go[0] = Gm;
-#pragma unroll
-    for (int e = 0; e < D; ++e) Go[(long long)(1 + e) * NE] = Gp[e];
-    Go[(long long)(D + 1) * NE] = Ge;
-
-    double* F = P.FP + (long long)d * NFP * NE + f;
-    F[PF_A * (long long)NE] = A;
-    F[PF_INV2RT * (long long)NE] = inv2RT;
-    F[PF_CRT2 * (long long)NE] = cRT2;
-    F[PF_IG * (long long)NE] = ig;
-    F[PF_IB * (long long)NE] = ib;
-    F[PF_EB * (long long)NE] = eta * ib;
-    F[PF_HU2 * (long long)NE] = hu2;
-#pragma unroll
-    for (int e = 0; e < 3; ++e) F[(PF_U0 + e) * (long long)NE] = q.u[e];
+    face_finish<D>(P, d, f, S, q, M);
 }
 
-template <int D>
-__device__ __forceinline__ void face_close_lanes(const Problem& P, long long t, double* red) {
+// L neighbouring threads per face.  What is long in a face's closure is the
+// exponential per node of each velocity axis and the sums over nodes and over
+// velocity slices.  The threads of the group share the exponentials, a chunk
+// of nodes at a time, through LDS; then each of its first 5D threads runs one
+// moment's sum over the chunk, and before that each of the first 2D+3 one
+// velocity sum over the slices.  Every sum is added up in the order of the
+// one-thread form, so the group size never changes a result.  With one thread
+// per face a step of the 128 x 16385 sine wave spent 2.86 ms of its 3.31 ms in
+// this closure, on 1/500 of the device's threads.
+// The sums are what is left then, one dependent FMA per node: their operands
+// are read 16 nodes ahead, two per LDS access, so an axis is padded to blocks
+// of 16 with nodes that add exact zeros.
+constexpr int CLOSE_BLOCK = 16;
+template <int L>
+struct CloseShared {
+    static constexpr int NF = WG / L;     // faces per workgroup
+    static constexpr int C = 2 * L;       // nodes of a chunk
+    static constexpr int ROW = C + 2;     // rows 16 bytes past a multiple of the banks
+    double t[NF][5][ROW];                 // w e, w e x, w e x^2, w e x^3, x
+    double s[NF][16];                     // velocity sums, then moments
+    double one[CLOSE_BLOCK];
+};
+constexpr int CLOSE_LDS_DOUBLES = 5 * (2 * WG + 2 * WG / 16) + WG + CLOSE_BLOCK;  // the largest is at L = 16
+template <int D, int L>
+__device__ __forceinline__ void face_close_group(const Problem& P, long long t, double* lds) {
+    constexpr int NS = 2 * D + 3;
+    using Sh = CloseShared<L>;
+    static_assert(NS <= 16 && 5 * D <= 16 && L >= 16, "a group runs its sums one per thread");
+    static_assert(sizeof(Sh) <= CLOSE_LDS_DOUBLES * sizeof(double), "closure LDS");
+    static_assert(Sh::C % CLOSE_BLOCK == 0, "chunks of whole blocks");
+    Sh& sm = *reinterpret_cast<Sh*>(lds);
+    const unsigned NE = (unsigned)P.NE;
+    const long long idx = t / L;  // face counted over the normals
+    const int fi = (int)threadIdx.x / L, lane = (int)threadIdx.x % L;
+    // every thread takes part in the barriers; a group without a face works
+    // on face 0 and writes nothing
+    bool valid = idx < (long long)NE * D;
+    const int d = valid ? (int)(idx / NE) : 0;
+    const unsigned f = valid ? (unsigned)(idx - (long long)d * NE) : 0;
+    valid = valid && face_in_grid<D>(P, d, f);
+
+    // nodes of the axes, each padded to whole blocks, one axis after another;
+    // a padding node has weight 0 at x = 0
+    auto padded = [](int n) { return (n + CLOSE_BLOCK - 1) / CLOSE_BLOCK * CLOSE_BLOCK; };
+    const int e1 = padded(P.nv[0]), e2 = e1 + (D >= 2 ? padded(P.nv[1]) : 0), e3 = e2 + (D >= 3 ? padded(P.nv[2]) : 0);
+    double nx[2], nw[2];  // this thread's nodes of the next chunk
+    int na[2];            // and their axes (-1: padding)
+    const int v0n = P.nv[0], v1n = P.nv[1], v2n = P.nv[2];
+    auto load_nodes = [&](int c0) __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int v = c0 + lane + j * L;
+            // position on its axis, the axis' length and its place in the tables
+            int ax = 0, m = v, n = v0n, at = 0;
+            if (D >= 2 && v >= e1) ax = 1, m = v - e1, n = v1n, at = v0n;
+            if (D >= 3 && v >= e2) ax = 2, m = v - e2, n = v2n, at = v0n + v1n;
+            const bool in = m < n;
+            const int i = in ? at + m : 0;
+            na[j] = in ? ax : -1;
+            nx[j] = P.axis_xi[i];
+            nw[j] = P.axis_w[i];
+        }
+    };
+    load_nodes(0);
+
+    // velocity sums over the slices: the group's threads fetch as many slices
+    // as fit the LDS at once, then each of the first NS adds its column up
+    if (threadIdx.x < CLOSE_BLOCK) sm.one[threadIdx.x] = 1.0;
+    {
+        constexpr int NR = 8;             // loads in flight per thread
+        constexpr int SC = NR * L / NS;   // slices at once
+        static_assert(SC * NS <= 5 * Sh::ROW, "slices of a pass fit the group's LDS");
+        double* const part = &sm.t[fi][0][0];
+        const double* const in = P.FS + (long long)d * NS * NE + f;
+        double a = 0.0;
+        for (int s0 = 0; s0 < P.nslices; s0 += SC) {
+            const int ns = P.nslices - s0 < SC ? P.nslices - s0 : SC;
+            double r[NR];
+#pragma unroll
+            for (int k = 0; k < NR; ++k) {
+                // past the pass' last value: reload the first, not stored
+                const int i = lane + k * L < ns * NS ? lane + k * L : 0;
+                const int s = i / NS, j = i - s * NS;
+                r[k] = in[((long long)(s0 + s) * D * NS + j) * NE];
+            }
+#pragma unroll
+            for (int k = 0; k < NR; ++k)
+                if (lane + k * L < ns * NS) part[lane + k * L] = r[k];
+            __syncthreads();
+            if (lane < NS) {
+#pragma unroll 8
+                for (int s = 0; s < ns; ++s) a += part[s * NS + lane];
+            }
+            __syncthreads();
+        }
+        if (lane < NS) sm.s[fi][lane] = a;
+    }
+    __syncthreads();
+    double S[NS];
+#pragma unroll
+    for (int j = 0; j < NS; ++j) S[j] = sm.s[fi][j];
+    const Prim q = face_primitives<D>(P, S);
+    if (valid && q.bad) {
+        if (lane == 0) raise_error(P.err);
+        valid = false;
+    }
+    const double inv2RT = 0.5 / q.RT;
+    // this thread's sum: moment p of axis k, over padded nodes [a0, a1)
+    const int k = lane / 5, p = lane % 5;
+    const int a0 = k == 0 ? 0 : (k == 1 ? e1 : e2);
+    const int a1 = lane >= 5 * D ? a0 : (k == 0 ? e1 : (k == 1 ? e2 : e3));
+    const int row = p == 0 ? 0 : p - 1;
+    // second factors: x, for p = 0 ones (M + e, exactly)
+    const double* const xs = p == 0 ? sm.one : sm.t[fi][4];
+    const int xstep = p == 0 ? 0 : 1;
+    double M = 0.0;
+    for (int c0 = 0; c0 < e3; c0 += Sh::C) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int o = lane + j * L;
+            const double uk = D == 1 || na[j] <= 0 ? q.u[0] : (D == 2 || na[j] == 1 ? q.u[1] : q.u[2]);
+            double x = nx[j];
+            double e = nw[j] * exp(-(x - uk) * (x - uk) * inv2RT);
+            if (na[j] < 0) x = e = 0.0;
+            sm.t[fi][0][o] = e;
+            sm.t[fi][1][o] = e * x;
+            sm.t[fi][2][o] = e * x * x;
+            sm.t[fi][3][o] = e * x * x * x;
+            sm.t[fi][4][o] = x;
+        }
+        load_nodes(c0 + Sh::C);  // in flight behind this chunk's sums
+        __syncthreads();
+        const int m0 = (a0 > c0 ? a0 : c0) - c0, m1 = (a1 < c0 + Sh::C ? a1 : c0 + Sh::C) - c0;
+        if (m0 < m1) {
+            double A[2][CLOSE_BLOCK], X[2][CLOSE_BLOCK];
+            auto load = [&](int m, int h) __attribute__((always_inline)) {
+                const double2* a = reinterpret_cast<const double2*>(&sm.t[fi][row][m]);
+                const double2* x = reinterpret_cast<const double2*>(xs + xstep * m);
+#pragma unroll
+                for (int j = 0; j < CLOSE_BLOCK / 2; ++j) {
+                    const double2 va = a[j], vx = x[j];
+                    A[h][2 * j] = va.x;
+                    A[h][2 * j + 1] = va.y;
+                    X[h][2 * j] = vx.x;
+                    X[h][2 * j + 1] = vx.y;
+                }
+            };
+            auto sum = [&](int h) __attribute__((always_inline)) {
+#pragma unroll
+                for (int j = 0; j < CLOSE_BLOCK; ++j) M = fma(A[h][j], X[h][j], M);
+            };
+            load(m0, 0);
+            int m = m0;
+            for (; m + CLOSE_BLOCK < m1; m += 2 * CLOSE_BLOCK) {
+                load(m + CLOSE_BLOCK, 1);
+                sum(0);
+                // past the last block: reload it, unused
+                load(m + 2 * CLOSE_BLOCK < m1 ? m + 2 * CLOSE_BLOCK : m, 0);
+                sum(1);
+            }
+            if (m < m1) sum(0);
+        }
+        __syncthreads();
+    }
+    if (lane < 5 * D) sm.s[fi][lane] = M;
+    __syncthreads();
+    if (lane != 0 || !valid) return;
+    double Mf[D][5];
+#pragma unroll
+    for (int e = 0; e < D; ++e)
+#pragma unroll
+        for (int j = 0; j < 5; ++j) Mf[e][j] = sm.s[fi][5 * e + j];
+    face_finish<D>(P, d, f, S, q, Mf);
+}
+
+// by group size
+template <int D, int L>
+__device__ __forceinline__ void face_close(const Problem& P, long long t, double* lds) {
+    if constexpr (L == 1) face_close_one<D>(P, t);
+    else face_close_group<D, L>(P, t, lds);
+}
+template <int D, bool GROUPS>
+__device__ __forceinline__ void face_close_lanes(const Problem& P, long long t, double* lds) {
+    if constexpr (!GROUPS) return face_close<D, 1>(P, t, lds);
     switch (P.close_lanes) {  // uniform per problem
-    case 1: face_close_group<D, 1>(P, t, red); break;
-    case 4: face_close_group<D, 4>(P, t, red); break;
-    case 16: face_close_group<D, 16>(P, t, red); break;
-    case 64: face_close_group<D, 64>(P, t, red); break;
-    default: face_close_group<D, 256>(P, t, red); break;
+    case 1: face_close<D, 1>(P, t, lds); break;
+    case 16: face_close<D, 16>(P, t, lds); break;
+    case 64: face_close<D, 64>(P, t, lds); break;
+    default: face_close<D, 256>(P, t, lds); break;
     }
 }
 

@@ -85,7 +85,7 @@ struct Problem {
     const long long* rows;
     int recon;    // 0: slopes of slopes (Sec. 2.1), 1: single slope
     int tile;     // face-sum tile shape (index into tile_shape(D, .))
-    int close_lanes;  // threads per face of the face closure: 1, 4, 16, 64 or 256 (= WG)
+    int close_lanes;  // threads per face of the face closure: 1, 16, 64 or 256 (= WG)
     int has_accel;     // external acceleration present (a != 0)
     double accel[3];   // external acceleration a (eqs. gPDE, bPDE)
 };
@@ -141,7 +141,7 @@ hipError_t launch_update_batched(const Problem* probs, const WorkItem* items, in
                                  int storage, bool accel, int* queue, int* other, hipStream_t s);
 int batched_blocks_per_cu(int maxd, int storage, bool accel, bool update);
 hipError_t launch_face_close_batched(const Problem* probs, const long long* offsets, int nprob, int maxd,
-                                     long long total, hipStream_t s);
+                                     bool groups, long long total, hipStream_t s);
 hipError_t launch_cell_close_batched(const Problem* probs, const long long* offsets, int nprob,
                                      long long total, hipStream_t s);
 

@@ -216,29 +216,31 @@ __global__ __launch_bounds__(WG) void k_update_batched(const Problem* probs, con
     }
 }
 
-template <int D>
+template <int D, int L>
 __global__ __launch_bounds__(WG) void k_face_close(Problem P) {
-    __shared__ double red[WG / 64];
-    face_close_lanes<D>(P, (long long)blockIdx.x * WG + threadIdx.x, red);
+    __shared__ __align__(16) double lds[L == 1 ? 2 : CLOSE_LDS_DOUBLES];
+    // consecutive faces share the lines of their partial sums: one XCD's L2
+    face_close<D, L>(P, (long long)xcd_remap(blockIdx.x, gridDim.x) * WG + threadIdx.x, lds);
 }
 
 // Batched closures: every problem's range of threads starts on a workgroup
 // boundary (offsets in threads, multiples of WG), so a workgroup serves one
 // problem, found once per workgroup (its descriptor then read at one address
 // by every lane); threads past the problem's faces (cells) return.  MAXD is
-// the largest dimension of the batch.
-template <int MAXD>
+// the largest dimension of the batch, GROUPS whether any of its faces is closed
+// by a group (whose registers the one-thread form does not need).
+template <int MAXD, bool GROUPS>
 __global__ __launch_bounds__(WG) void k_face_close_batched(const Problem* probs, const long long* offsets,
                                                            int nprob, long long total) {
-    __shared__ double red[WG / 64];
+    __shared__ __align__(16) double lds[GROUPS ? CLOSE_LDS_DOUBLES : 2];
     const long long g0 = (long long)blockIdx.x * WG;
     if (g0 >= total) return;
     const int p = __builtin_amdgcn_readfirstlane(find_problem(offsets, nprob, g0));
     const Problem& P = probs[p];  // by reference: no private copy
     const long long t = g0 - offsets[p] + threadIdx.x;
-    if (P.D == 1) face_close_lanes<1>(P, t, red);
-    else if (MAXD >= 2 && P.D == 2) face_close_lanes<MAXD >= 2 ? 2 : 1>(P, t, red);
-    else if (MAXD >= 3) face_close_lanes<MAXD >= 3 ? 3 : 1>(P, t, red);
+    if (P.D == 1) face_close_lanes<1, GROUPS>(P, t, lds);
+    else if (MAXD >= 2 && P.D == 2) face_close_lanes<MAXD >= 2 ? 2 : 1, GROUPS>(P, t, lds);
+    else if (MAXD >= 3) face_close_lanes<MAXD >= 3 ? 3 : 1, GROUPS>(P, t, lds);
 }
 
 template <int D>
@@ -405,9 +407,17 @@ int tile_blocks_per_cu(int D, int storage, bool update) {
 
 hipError_t launch_face_close(const Problem& P, hipStream_t s) {
     const dim3 grid(blocks_for(P.NE * P.D * P.close_lanes));
-    if (P.D == 1) hipLaunchKernelGGL(k_face_close<1>, grid, dim3(WG), 0, s, P);
-    else if (P.D == 2) hipLaunchKernelGGL(k_face_close<2>, grid, dim3(WG), 0, s, P);
-    else hipLaunchKernelGGL(k_face_close<3>, grid, dim3(WG), 0, s, P);
+#define CDG_L(D)                                                                                          \
+    do {                                                                                                  \
+        if (P.close_lanes == 1) hipLaunchKernelGGL((k_face_close<D, 1>), grid, dim3(WG), 0, s, P);        \
+        else if (P.close_lanes == 16) hipLaunchKernelGGL((k_face_close<D, 16>), grid, dim3(WG), 0, s, P); \
+        else if (P.close_lanes == 64) hipLaunchKernelGGL((k_face_close<D, 64>), grid, dim3(WG), 0, s, P); \
+        else hipLaunchKernelGGL((k_face_close<D, 256>), grid, dim3(WG), 0, s, P);                         \
+    } while (0)
+    if (P.D == 1) CDG_L(1);
+    else if (P.D == 2) CDG_L(2);
+    else CDG_L(3);
+#undef CDG_L
     return hipGetLastError();
 }
 
@@ -483,12 +493,20 @@ int batched_blocks_per_cu(int maxd, int storage, bool accel, bool update) {
 }
 
 hipError_t launch_face_close_batched(const Problem* probs, const long long* offsets, int nprob, int maxd,
-                                     long long total, hipStream_t s) {
+                                     bool groups, long long total, hipStream_t s) {
     if (total <= 0) return hipSuccess;
     const dim3 grid(blocks_for(total));
-    if (maxd == 1) hipLaunchKernelGGL(k_face_close_batched<1>, grid, dim3(WG), 0, s, probs, offsets, nprob, total);
-    else if (maxd == 2) hipLaunchKernelGGL(k_face_close_batched<2>, grid, dim3(WG), 0, s, probs, offsets, nprob, total);
-    else hipLaunchKernelGGL(k_face_close_batched<3>, grid, dim3(WG), 0, s, probs, offsets, nprob, total);
+#define CDG_L(MD)                                                                                                \
+    do {                                                                                                         \
+        if (groups)                                                                                              \
+            hipLaunchKernelGGL((k_face_close_batched<MD, true>), grid, dim3(WG), 0, s, probs, offsets, nprob, total);  \
+        else                                                                                                     \
+            hipLaunchKernelGGL((k_face_close_batched<MD, false>), grid, dim3(WG), 0, s, probs, offsets, nprob, total); \
+    } while (0)
+    if (maxd == 1) CDG_L(1);
+    else if (maxd == 2) CDG_L(2);
+    else CDG_L(3);
+#undef CDG_L
     return hipGetLastError();
 }
 hipError_t launch_cell_close_batched(const Problem* probs, const long long* offsets, int nprob,

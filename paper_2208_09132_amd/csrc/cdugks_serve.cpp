@@ -141,6 +141,7 @@ struct cdugks_batch {
     long long* d_cell_off = nullptr;
     long long face_total = 0, cell_total = 0;
     int maxd = 1;  // largest dimension
+    bool close_groups = false;  // some problem's faces are closed by groups of threads
     std::vector<StorageClass> classes;
     hipGraphExec_t graph[2] = {nullptr, nullptr};
     std::vector<hipStream_t> others;  // streams of members other than the batch stream
@@ -157,7 +158,8 @@ hipError_t enqueue_batch_step(cdugks_batch* b, int phase) {
         if ((e = launch_face_sums_batched(probs, c.items_fs, c.n_fs, c.grid_fs, c.maxd, c.storage, c.dirichlet,
                                           c.single_slope, c.accel, c.queue, c.queue + 1, b->stream)) != hipSuccess)
             return e;
-    if ((e = launch_face_close_batched(probs, b->d_face_off, np, b->maxd, b->face_total, b->stream)) != hipSuccess)
+    if ((e = launch_face_close_batched(probs, b->d_face_off, np, b->maxd, b->close_groups, b->face_total,
+                                       b->stream)) != hipSuccess)
         return e;
     if ((e = launch_cell_close_batched(probs, b->d_cell_off, np, b->cell_total, b->stream)) != hipSuccess) return e;
     for (auto& c : b->classes)
@@ -245,9 +247,14 @@ int batch_build(cdugks_ctx* const* ctxs, int count, int chunk_steps, cdugks_batc
     // host tables
     std::vector<Problem> probs[2];
     std::vector<long long> face_off(count), cell_off(count);
-    long long ft = 0, ct = 0;
+    long long ft = 0, ct = 0, faces = 0;
+    for (int j = 0; j < count; ++j) faces += ctxs[j]->r.NE * ctxs[j]->r.D;
     for (int j = 0; j < count; ++j) {
         cdugks_ctx* c = ctxs[j];
+        // the batch's faces together decide the closure's group sizes (which
+        // never change a result)
+        const int lanes = close_lanes(c->r, faces);
+        if (lanes > 1) b->close_groups = true;
         for (int p = 0; p < 2; ++p) {
             Problem P = c->P;
             set_pingpong(P, c->r, c->base, c->cur ^ p);
@@ -255,13 +262,14 @@ int batch_build(cdugks_ctx* const* ctxs, int count, int chunk_steps, cdugks_batc
             // dimension and storage form (the same result as any other shape)
             P.tile = batched_face_tile(c->r.D, c->r.storage);
             for (int d = 0; d < 3; ++d) P.tiles1[d] = batched_tiles(c->r, d);
+            P.close_lanes = lanes;
             probs[p].push_back(P);
         }
         b->maxd = std::max(b->maxd, c->r.D);
         face_off[j] = ft;
         cell_off[j] = ct;
         // each problem's closure threads start on a workgroup boundary
-        ft += (c->r.NE * c->r.D * c->P.close_lanes + WG - 1) / WG * WG;
+        ft += (c->r.NE * c->r.D * lanes + WG - 1) / WG * WG;
         ct += (c->r.N + WG - 1) / WG * WG;
     }
     b->face_total = ft;

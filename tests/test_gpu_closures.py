@@ -1,12 +1,13 @@
-"""The face closure's groups of threads (1, 4, 16, 64 or a whole workgroup per
-face, chosen from the face count and the longest serial sum) and the cell
-closure inside the update, against the FP64 oracle: moments within 1e-12 and
-g, b within 1e-12 of each velocity row's largest value, the parity bound of
-the other FP64 tests (the sums of a face are the same numbers added in another
-order, at most a few hundred ulp).  Each size sits at an edge of the rule: the
-last velocity count of one group size and the first of the next, counts the
-group does not divide, the face count from which one thread takes a face, and
-faces outside the grid (outflow) beside groups that close theirs."""
+"""The face closure's groups of threads (one thread, 16, 64 or a whole
+workgroup per face, chosen from the face count and the number of velocity
+nodes) and the cell closure inside the update, against the FP64 oracle:
+moments within 1e-12 and g, b within 1e-12 of each velocity row's largest
+value, the parity bound of the other FP64 tests (a group adds up in the order
+of one thread, so no bound of its own is needed).  Each size sits at an edge of
+the rule or of the groups' work: node counts at and past a chunk, blocks of 16
+nodes left partly empty, more velocity slices than one pass over them holds,
+the face count from which one thread takes a face, and faces outside the grid
+(outflow) beside groups that close theirs."""
 import numpy as np
 import pytest
 
@@ -25,21 +26,24 @@ def problem(n, nv, bc=None, accel=None):
     return p
 
 
-@pytest.mark.parametrize("n, nv, bc, accel", [
-    ([5], [31], None, None),                # 4 threads per face
-    ([7], [33], ["outflow"], [0.5]),        # 16, one node left over
-    ([130], [127], None, None),             # 16, its longest
-    ([3], [128], ["outflow"], None),        # 64
-    ([9], [511], None, [0.3]),              # 64, its longest
-    ([1], [513], ["outflow"], None),        # a workgroup per face
-    ([33], [2050], None, [0.3]),            # a workgroup per face, ragged
-    ([6, 5], [33, 9], ["outflow", "periodic"], [0.2, -0.1]),
-    ([3, 4], [9, 129], ["periodic", "outflow"], None),
-    ([512, 256], [7, 7], None, None),       # 2^18 faces: one thread per face
-    ([3, 4, 5], [33, 9, 9], ["outflow", "outflow", "periodic"], [0.1, 0.2, -0.1]),
+@pytest.mark.parametrize("n, nv, bc, accel, slices", [
+    ([5], [31], None, None, 0),                # 16 threads per face
+    ([7], [33], ["outflow"], [0.5], 33),       # 64, one node past two blocks, a slice per velocity
+    ([130], [128], None, None, 128),           # 64, a whole chunk, more slices than a pass
+    ([3], [129], ["outflow"], None, 0),        # a workgroup, one node past
+    ([600], [511], None, [0.3], 70),           # 64, several chunks
+    ([1], [513], ["outflow"], None, 513),      # a workgroup, one node past a chunk
+    ([33], [2050], None, [0.3], 0),            # a workgroup per face, ragged
+    ([6, 5], [33, 9], ["outflow", "periodic"], [0.2, -0.1], 60),
+    ([3, 4], [9, 129], ["periodic", "outflow"], None, 0),
+    ([40, 50], [17, 16], ["periodic", "outflow"], None, 5),  # 16, more than one chunk
+    ([256, 128], [7, 7], None, None, 0),       # 2^16 faces: one thread per face
+    ([3, 4, 5], [33, 9, 9], ["outflow", "outflow", "periodic"], [0.1, 0.2, -0.1], 0),
 ])
-def test_closures_match_the_oracle(n, nv, bc, accel):
-    parity(problem(n, nv, bc, accel), 3, 1e-12, distributions=True)
+def test_closures_match_the_oracle(n, nv, bc, accel, slices):
+    p = problem(n, nv, bc, accel)
+    p["velocity_slices"] = slices
+    parity(p, 3, 1e-12, distributions=True)
 
 
 def test_closures_in_a_batch_equal_solo_runs():
