@@ -207,13 +207,25 @@ int batched_tiles(const Resolved& r, int d) {
 
 // Velocity slices of a problem's update items in a batch: the autotuner's
 // split for the problem's class when it has one (its trials time this very
-// path), else at least BATCH_UPD_VELOCITIES velocities per item (all of them
-// for smaller velocity sets), never more slices than the problem's own plan.
-constexpr int BATCH_UPD_VELOCITIES = 256;
-int batch_update_slices(const Resolved& r) {
+// path), else slices of about `velocities` velocities.
+int batch_update_slices(const Resolved& r, long long velocities) {
     if (const int tu = tune_lookup(r).upd_slices; tu > 0) return (int)std::min<long long>(tu, r.V);
-    const long long s = std::max(1LL, r.V / BATCH_UPD_VELOCITIES);
-    return (int)std::min<long long>(s, std::max(1, r.nslices_upd));
+    return (int)std::max(1LL, r.V / velocities);
+}
+// Velocities per update item of a class: what spreads its (block, velocity)
+// pairs over the resident workgroups in two rounds, within
+// [BATCH_UPD_LEAST, BATCH_UPD_MOST].  Every item loads its cells' and their
+// faces' coefficient sets once, which short items pay for over and over; but
+// a class of few problems needs them, or most of the device stays idle (a
+// batch of one 137^2 x 20^2 problem at 256 velocities per item ran its update
+// in 74 workgroups, 339 us against 66 us alone).  Two rounds:
+// five problems of 92^2..125^2 cells take 659 us per step (915 at 256, 667 with
+// one round, 646 with four), 20 uneven ones 2.19 ms (2.30 at 256); four rounds
+// give 2.09 ms, but the reloads cost 1% where several batches share the device.
+constexpr long long BATCH_UPD_LEAST = 32, BATCH_UPD_MOST = 256, BATCH_UPD_ROUNDS = 2;
+long long batch_update_velocities(long long block_velocities, long long resident) {
+    const long long v = block_velocities / std::max(1LL, BATCH_UPD_ROUNDS * resident);
+    return std::min(BATCH_UPD_MOST, std::max(BATCH_UPD_LEAST, v));
 }
 
 // Build device tables for a set of contexts.
@@ -281,6 +293,7 @@ int batch_build(cdugks_ctx* const* ctxs, int count, int chunk_steps, cdugks_batc
     std::vector<std::vector<WorkItem>> fs(NCLASS), up(NCLASS);
     std::vector<std::vector<double>> cfs(NCLASS), cup(NCLASS);
     int maxd[NCLASS] = {};
+    long long block_vel[NCLASS] = {};  // update blocks x velocities of the class
     auto class_of = [](const Resolved& r) {
         return ((2 * r.storage + (r.any_dirichlet ? 1 : 0)) * 2 + r.recon) * 2 + (r.has_accel ? 1 : 0);
     };
@@ -288,6 +301,18 @@ int batch_build(cdugks_ctx* const* ctxs, int count, int chunk_steps, cdugks_batc
         const Resolved& r = ctxs[j]->r;
         const int s = class_of(r);
         maxd[s] = std::max(maxd[s], r.D);
+        block_vel[s] += (r.N + WG - 1) / WG * r.V;
+    }
+    const int cus = device_cus();
+    long long per_item[NCLASS];
+    for (int s = 0; s < NCLASS; ++s)
+        per_item[s] = maxd[s] ? batch_update_velocities(
+                                    block_vel[s], (long long)cus * std::max(1, batched_blocks_per_cu(
+                                                                                   maxd[s], s / 8, s % 2 == 1, true)))
+                              : BATCH_UPD_MOST;
+    for (int j = 0; j < count; ++j) {
+        const Resolved& r = ctxs[j]->r;
+        const int s = class_of(r);
         const int nt = batched_tiles(r, 0) * batched_tiles(r, 1) * batched_tiles(r, 2);
         const double vpt = (double)r.V / r.nslices;
         for (int sl = 0; sl < r.nslices; ++sl)
@@ -296,12 +321,9 @@ int batch_build(cdugks_ctx* const* ctxs, int count, int chunk_steps, cdugks_batc
                 cfs[s].push_back(vpt * r.D * (r.D + 1));
             }
         // Update items take the batch's own velocity split: the update forms
-        // no sums, so its split never changes a result, and the batch has
-        // work enough to fill the device without the many short slices a
-        // small problem uses alone, each of which loads the cell's and its
-        // faces' coefficient sets again.
+        // no sums, so its split never changes a result.
         const int nb = (int)((r.N + WG - 1) / WG);
-        const int us = batch_update_slices(r);
+        const int us = batch_update_slices(r, per_item[s]);
         const double vpu = (double)r.V / us;
         for (int sl = 0; sl < us; ++sl)
             for (int t = 0; t < nb; ++t) {
@@ -360,7 +382,6 @@ int batch_build(cdugks_ctx* const* ctxs, int count, int chunk_steps, cdugks_batc
     b->d_probs[1] = (Problem*)(b->dev + o_p1);
     b->d_face_off = (long long*)(b->dev + o_fo);
     b->d_cell_off = (long long*)(b->dev + o_co);
-    const int cus = device_cus();
     for (int s = 0; s < NCLASS; ++s) {
         if (fs[s].empty()) continue;
         StorageClass sc;
