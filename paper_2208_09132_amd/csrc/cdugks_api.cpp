@@ -242,6 +242,11 @@ int resolve(const cdugks_space* sp, const cdugks_velocity* ve, const cdugks_para
     long long s1 = slices > 0 ? std::min<long long>(slices, r.V) : plan(nt1, R1);
     r.nslices = (int)std::max(1LL, s1);
     r.nslices_upd = (int)std::max(1LL, plan(nt2, R2));
+    // The update forms no sums, so its split is free: one that leaves half of
+    // the device idle is made finer, down to 4 velocities per slice (a slice
+    // costs its cells' and faces' coefficients, about 5 us, a velocity 1 us).
+    if (nt2 * r.nslices_upd <= R2 / 2)
+        r.nslices_upd = (int)std::max<long long>(r.nslices_upd, std::min(R2 / nt2, r.V / 4));
     // the autotuner may have picked another update split for this class
     // (speed only: the update's result does not depend on it)
     if (int tu = tuned_update_slices(r); tu > 0) r.nslices_upd = (int)std::min<long long>(tu, r.V);
@@ -462,15 +467,33 @@ void dirichlet_tables(const Resolved& r, const std::vector<double>& vel, std::ve
     }
 }
 
+// Velocity slices of the face-value launch of a problem that leaves most of
+// the device idle (1-D and 2-D, tile shape 0; 0: face values and sums in one
+// launch).  The slices of the sums fix their order and number of workgroups;
+// storing the values first, in slices down to 4 velocities, and summing them
+// in a second launch gives the same sums from as many workgroups as the device
+// holds.  A velocity takes a workgroup about 1.1 us whatever else runs, the
+// second launch 5 to 10 us.
+int value_slices(const Resolved& r) {
+    if (r.D == 3 || r.tile != 0) return 0;
+    long long R1, R2;
+    resident_slots(r.D, r.storage, &R1, &R2);
+    const long long tiles = (long long)r.tiles1[0] * r.tiles1[1];
+    const long long s = std::min<long long>(R1 / std::max(1LL, tiles), r.V / 4);
+    return s >= 2 * r.nslices && r.V / r.nslices >= 12 ? (int)s : 0;
+}
+
 // Threads per face of the face closure (speed only), of a launch that closes
-// `faces` faces.  One where those fill the device, unless a face's nodes are
-// so many that its thread would outlast the launch; else groups that share a
-// face's nodes: larger ones for longer axes, as long as two workgroups per CU
-// hold them all.
+// `faces` faces: groups that share a face's nodes, larger ones for longer
+// axes, as long as two workgroups per CU hold them all.  One thread per face
+// where not even the smallest groups have that room, unless a face's nodes are
+// so many that its thread would outlast theirs (16 threads against one: 7.9
+// and 12 us for 64^2 cells x 16^2 velocities, 8192 faces; 27 and 16 us for
+// 96^2 x 20^2; 25 us both for 20000 faces of 129 nodes).
 int close_lanes(const Resolved& r, long long faces) {
-    constexpr long long MANY_FACES = 1 << 16, ROOM = 256 * 2 * WG;
+    constexpr long long ROOM = 256 * 2 * WG;
     const int nodes = (r.D >= 1 ? r.nv[0] : 0) + (r.D >= 2 ? r.nv[1] : 0) + (r.D >= 3 ? r.nv[2] : 0);
-    if (faces >= MANY_FACES && nodes <= 256) return 1;
+    if (16 * faces > ROOM && nodes <= 256) return 1;
     int l = 16;
     while (l < WG && nodes > 2 * l && 4 * l * faces <= ROOM) l *= 4;
     return l;
@@ -524,6 +547,7 @@ void fill_problem(const Resolved& r, char* base, Problem& P) {
     P.rows = r.storage == CDUGKS_STORE_F32_BF16TAIL ? (const long long*)(base + r.off_rows) : nullptr;
     P.recon = r.recon;
     P.tile = r.tile;
+    P.value_slices = value_slices(r);
     P.close_lanes = close_lanes(r, r.NE * r.D);
     P.has_accel = r.has_accel ? 1 : 0;
     for (int d = 0; d < 3; ++d) P.accel[d] = r.accel[d];

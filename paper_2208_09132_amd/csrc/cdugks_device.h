@@ -608,7 +608,9 @@ struct GaussWalk {
 // cell's slopes).
 // ACC: the problem has an external acceleration (stage 1 adds its source
 // terms; the a = 0 instantiations keep their register budget).
-template <int D, typename ST, bool DIR = false, bool SS = false, int TID = 0, bool ACC = false>
+// SUMS: the thread accumulates its faces' velocity sums over the slice;
+// without, it stores the face values only (k_face_reduce sums them).
+template <int D, typename ST, bool DIR = false, bool SS = false, int TID = 0, bool ACC = false, bool SUMS = true>
 struct FaceSumKernel {
     using G = Geo<D, TID>;
     static constexpr int NT = G::NT;
@@ -754,11 +756,13 @@ struct FaceSumKernel {
         }
 
         constexpr int NS = 2 * D + 3;
-        double acc[D][NS];
+        double acc[SUMS ? D : 1][NS];
+        if constexpr (SUMS) {
 #pragma unroll
-        for (int d = 0; d < D; ++d)
+            for (int d = 0; d < D; ++d)
 #pragma unroll
-            for (int j = 0; j < NS; ++j) acc[d][j] = 0.0;
+                for (int j = 0; j < NS; ++j) acc[d][j] = 0.0;
+        }
 
         // Software pipelining: the next velocity's fields are loaded while the
         // current one is processed (when the q-box slots fit in registers).
@@ -963,15 +967,17 @@ struct FaceSumKernel {
                     st_stream<CT>(P.FV, o, vg);
                     st_stream<CT>(P.FV, o + fstride, vb2);
                 }
-                // weighted velocity products come from the table (uniform)
-                const const_dptr vp = vel_ptr(P.vel, i);
-                acc[d][0] += v.w * vg;
+                if constexpr (SUMS) {
+                    // weighted velocity products come from the table (uniform)
+                    const const_dptr vp = vel_ptr(P.vel, i);
+                    acc[d][0] += v.w * vg;
 #pragma unroll
-                for (int e = 0; e < D; ++e) acc[d][1 + e] += vp[VE_WXI0 + e] * vg;
-                acc[d][D + 1] += v.w * vb2;
+                    for (int e = 0; e < D; ++e) acc[d][1 + e] += vp[VE_WXI0 + e] * vg;
+                    acc[d][D + 1] += v.w * vb2;
 #pragma unroll
-                for (int e = 0; e < D; ++e) acc[d][D + 2 + e] += vp[VE_WXX + 3 * d + e] * vg;
-                acc[d][2 * D + 2] += vp[VE_WXI0 + d] * vb2;
+                    for (int e = 0; e < D; ++e) acc[d][D + 2 + e] += vp[VE_WXX + 3 * d + e] * vg;
+                    acc[d][2 * D + 2] += vp[VE_WXI0 + d] * vb2;
+                }
             }
             if constexpr (WALKER) {
 #pragma unroll
@@ -1011,12 +1017,14 @@ struct FaceSumKernel {
         }
 
         // partial face sums of this velocity slice
+        if constexpr (SUMS) {
 #pragma unroll
-        for (int d = 0; d < D; ++d) {
-            if (!fvalid[d]) continue;
-            double* out = P.FS + ((long long)(slice * D + d) * NS) * NE + fe;
+            for (int d = 0; d < D; ++d) {
+                if (!fvalid[d]) continue;
+                double* out = P.FS + ((long long)(slice * D + d) * NS) * NE + fe;
 #pragma unroll
-            for (int j = 0; j < NS; ++j) out[(long long)j * NE] = acc[d][j];
+                for (int j = 0; j < NS; ++j) out[(long long)j * NE] = acc[d][j];
+            }
         }
     }
 };
@@ -1347,15 +1355,87 @@ template <int D>
 constexpr int face_sum_waves() { return D == 1 ? 4 : (D == 2 ? 3 : 1); }
 
 // The single-problem face-sum kernel of tile shape TID.
-template <int D, typename ST, bool DIR, bool SS, int TID, bool ACC>
+template <int D, typename ST, bool DIR, bool SS, int TID, bool ACC, bool SUMS = true>
 __global__ __launch_bounds__(tile_threads(D, TID), face_sum_waves<D>()) void k_face_sums(Problem P) {
-    using K = FaceSumKernel<D, ST, DIR, SS, TID, ACC>;
+    using K = FaceSumKernel<D, ST, DIR, SS, TID, ACC, SUMS>;
     static_assert(sizeof(typename K::Smem) == face_sum_lds_bytes(D, TID, sizeof(typename K::CT)),
                   "host and kernel LDS sizes differ");
     __shared__ typename K::Smem sm;
     int ntiles = P.tiles1[0] * P.tiles1[1] * P.tiles1[2];
     int q = xcd_remap(blockIdx.x, gridDim.x);
-    K::run(P, q % ntiles, q / ntiles, P.nslices, sm);
+    K::run(P, q % ntiles, q / ntiles, SUMS ? P.nslices : P.value_slices, sm);
+}
+
+// Velocity sums of the stored face values of one velocity slice: per face
+// along d, the 2D+3 sums of the box kernel with the same products in the same
+// ascending-velocity order, so the partial sums are bitwise those the box
+// kernel accumulates in registers.  One thread per face-grid point takes its
+// D faces.
+template <int D, typename CT, int TB, int UNROLL>
+__global__ __launch_bounds__(TB) void k_face_reduce(Problem P) {
+    const long long fe = (long long)blockIdx.x * TB + threadIdx.x;
+    const int slice = blockIdx.y;
+    if (fe >= P.NE) return;
+    const int c[3] = {(int)(fe % P.ne[0]), (int)((fe / P.ne[0]) % P.ne[1]),
+                      (int)(fe / ((long long)P.ne[0] * P.ne[1]))};
+    bool valid[D];
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+        bool ok = true;
+#pragma unroll
+        for (int e = 0; e < D; ++e) ok &= e == d ? c[e] < P.ne[e] : c[e] < P.n[e];
+        valid[d] = ok;
+    }
+    const int v0 = (int)((long long)P.V * slice / P.nslices);
+    const int v1 = (int)((long long)P.V * (slice + 1) / P.nslices);
+    constexpr int NS = 2 * D + 3;
+    double acc[D][NS];
+#pragma unroll
+    for (int d = 0; d < D; ++d)
+#pragma unroll
+        for (int j = 0; j < NS; ++j) acc[d][j] = 0.0;
+    const CT* const fv = (const CT*)P.FV + fe;
+#pragma unroll UNROLL
+    for (int i = v0; i < v1; ++i) {
+        const Vel v = load_vel(P.vel, i);
+        const const_dptr vp = vel_ptr(P.vel, i);
+        const long long row = (long long)i * P.fv_pitch;
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            // invalid faces read a stored slot of the block and discard it
+            const double vg = fv[(long long)(2 * d) * P.fv_stride + row];
+            const double vb2 = fv[(long long)(2 * d + 1) * P.fv_stride + row];
+            acc[d][0] += v.w * vg;
+#pragma unroll
+            for (int e = 0; e < D; ++e) acc[d][1 + e] += vp[VE_WXI0 + e] * vg;
+            acc[d][D + 1] += v.w * vb2;
+#pragma unroll
+            for (int e = 0; e < D; ++e) acc[d][D + 2 + e] += vp[VE_WXX + 3 * d + e] * vg;
+            acc[d][2 * D + 2] += vp[VE_WXI0 + d] * vb2;
+        }
+    }
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+        if (!valid[d]) continue;
+        double* out = P.FS + ((long long)(slice * D + d) * NS) * P.NE + fe;
+#pragma unroll
+        for (int j = 0; j < NS; ++j) out[(long long)j * P.NE] = acc[d][j];
+    }
+}
+
+template <int D, typename CT>
+hipError_t launch_face_reduce(const Problem& P, hipStream_t s) {
+    if constexpr (D <= 2) {
+        // few threads and long sums: single waves spread over the CUs, and
+        // enough velocities' values in flight to cover their latency
+        constexpr int TB = 64;
+        hipLaunchKernelGGL((k_face_reduce<D, CT, TB, D == 1 ? 16 : 8>), dim3((unsigned)((P.NE + TB - 1) / TB), P.nslices),
+                           dim3(TB), 0, s, P);
+    } else {
+        hipLaunchKernelGGL((k_face_reduce<D, CT, WG, 4>), dim3((unsigned)((P.NE + WG - 1) / WG), P.nslices), dim3(WG), 0,
+                           s, P);
+    }
+    return hipGetLastError();
 }
 
 // Launch the face sums of a problem of dimension D: the kernel of its tile
@@ -1365,8 +1445,18 @@ __global__ __launch_bounds__(tile_threads(D, TID), face_sum_waves<D>()) void k_f
 template <int D, typename ST, bool DIR, bool SS, int TID, bool ACC = false>
 hipError_t launch_face_sums_shape(const Problem& P, hipStream_t s) {
     if constexpr (face_tile_fits(D, TID, sizeof(typename StoreT<ST>::C))) {
-        const unsigned nb = (unsigned)(P.tiles1[0] * P.tiles1[1] * P.tiles1[2] * P.nslices);
-        hipLaunchKernelGGL((k_face_sums<D, ST, DIR, SS, TID, ACC>), dim3(nb), dim3(tile_threads(D, TID)), 0, s, P);
+        const unsigned nt = (unsigned)(P.tiles1[0] * P.tiles1[1] * P.tiles1[2]);
+        if constexpr (D <= 2 && TID == 0) {
+            if (P.value_slices > 0) {
+                hipLaunchKernelGGL((k_face_sums<D, ST, DIR, SS, TID, ACC, false>), dim3(nt * P.value_slices),
+                                   dim3(tile_threads(D, TID)), 0, s, P);
+                hipError_t e = hipGetLastError();
+                if (e != hipSuccess) return e;
+                return launch_face_reduce<D, typename StoreT<ST>::C>(P, s);
+            }
+        }
+        hipLaunchKernelGGL((k_face_sums<D, ST, DIR, SS, TID, ACC>), dim3(nt * P.nslices), dim3(tile_threads(D, TID)), 0,
+                           s, P);
         return hipGetLastError();
     } else {
         return hipErrorInvalidConfiguration;
@@ -1650,63 +1740,6 @@ __global__ __launch_bounds__((ZMarch<ST, DIR, SS, TX, TY>::NTH)) void k_face_val
     K::run(P, q % ntiles, q / ntiles, sm);
 }
 
-// Velocity sums of the stored face values of one velocity slice: per face
-// along d, the 2D+3 sums of the box kernel with the same products in the same
-// ascending-velocity order, so the partial sums are bitwise those the box
-// kernel accumulates in registers.  One thread per face-grid point takes its
-// D faces.
-template <int D, typename CT>
-__global__ __launch_bounds__(WG) void k_face_reduce(Problem P) {
-    const long long fe = (long long)blockIdx.x * WG + threadIdx.x;
-    const int slice = blockIdx.y;
-    if (fe >= P.NE) return;
-    const int c[3] = {(int)(fe % P.ne[0]), (int)((fe / P.ne[0]) % P.ne[1]),
-                      (int)(fe / ((long long)P.ne[0] * P.ne[1]))};
-    bool valid[D];
-#pragma unroll
-    for (int d = 0; d < D; ++d) {
-        bool ok = true;
-#pragma unroll
-        for (int e = 0; e < D; ++e) ok &= e == d ? c[e] < P.ne[e] : c[e] < P.n[e];
-        valid[d] = ok;
-    }
-    const int v0 = (int)((long long)P.V * slice / P.nslices);
-    const int v1 = (int)((long long)P.V * (slice + 1) / P.nslices);
-    constexpr int NS = 2 * D + 3;
-    double acc[D][NS];
-#pragma unroll
-    for (int d = 0; d < D; ++d)
-#pragma unroll
-        for (int j = 0; j < NS; ++j) acc[d][j] = 0.0;
-    const CT* const fv = (const CT*)P.FV + fe;
-#pragma unroll 4
-    for (int i = v0; i < v1; ++i) {
-        const Vel v = load_vel(P.vel, i);
-        const const_dptr vp = vel_ptr(P.vel, i);
-        const long long row = (long long)i * P.fv_pitch;
-#pragma unroll
-        for (int d = 0; d < D; ++d) {
-            // invalid faces read a stored slot of the block and discard it
-            const double vg = fv[(long long)(2 * d) * P.fv_stride + row];
-            const double vb2 = fv[(long long)(2 * d + 1) * P.fv_stride + row];
-            acc[d][0] += v.w * vg;
-#pragma unroll
-            for (int e = 0; e < D; ++e) acc[d][1 + e] += vp[VE_WXI0 + e] * vg;
-            acc[d][D + 1] += v.w * vb2;
-#pragma unroll
-            for (int e = 0; e < D; ++e) acc[d][D + 2 + e] += vp[VE_WXX + 3 * d + e] * vg;
-            acc[d][2 * D + 2] += vp[VE_WXI0 + d] * vb2;
-        }
-    }
-#pragma unroll
-    for (int d = 0; d < D; ++d) {
-        if (!valid[d]) continue;
-        double* out = P.FS + ((long long)(slice * D + d) * NS) * P.NE + fe;
-#pragma unroll
-        for (int j = 0; j < NS; ++j) out[(long long)j * P.NE] = acc[d][j];
-    }
-}
-
 // Face values by z-march, then their velocity sums (tile shape TID with z = 0).
 template <typename ST, bool DIR, bool SS, int TID>
 hipError_t launch_face_sums_zmarch(const Problem& P, hipStream_t s) {
@@ -1720,9 +1753,7 @@ hipError_t launch_face_sums_zmarch(const Problem& P, hipStream_t s) {
         hipLaunchKernelGGL((k_face_values_z<ST, DIR, SS, T.x, T.y>), dim3(nb), dim3(K::NTH), 0, s, P);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL((k_face_reduce<3, typename K::CT>), dim3((unsigned)((P.NE + WG - 1) / WG), P.nslices),
-                           dim3(WG), 0, s, P);
-        return hipGetLastError();
+        return launch_face_reduce<3, typename K::CT>(P, s);
     } else {
         return hipErrorInvalidConfiguration;
     }

@@ -50,6 +50,7 @@ int resolve(const cdugks_space* sp, const cdugks_velocity* ve, const cdugks_para
 void resident_slots(int D, int storage, long long* R1, long long* R2);
 void velocity_tables(const Resolved& r, std::vector<double>& vel, std::vector<double>& axis);
 void dirichlet_tables(const Resolved& r, const std::vector<double>& vel, std::vector<double>& out);
+int value_slices(const Resolved& r);
 int close_lanes(const Resolved& r, long long faces);
 // Device memory (cdugks_pool.cpp): a block of at least `bytes` and at most
 // `most` bytes, its size in *got, from the idle blocks of the current device

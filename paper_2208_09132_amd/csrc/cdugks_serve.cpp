@@ -275,6 +275,7 @@ int batch_build(cdugks_ctx* const* ctxs, int count, int chunk_steps, cdugks_batc
             P.tile = batched_face_tile(c->r.D, c->r.storage);
             for (int d = 0; d < 3; ++d) P.tiles1[d] = batched_tiles(c->r, d);
             P.close_lanes = lanes;
+            P.value_slices = 0;  // a batch fills the device with the slices of the sums
             probs[p].push_back(P);
         }
         b->maxd = std::max(b->maxd, c->r.D);
