@@ -547,6 +547,7 @@ void fill_problem(const Resolved& r, char* base, Problem& P) {
     P.rows = r.storage == CDUGKS_STORE_F32_BF16TAIL ? (const long long*)(base + r.off_rows) : nullptr;
     P.recon = r.recon;
     P.tile = r.tile;
+    P.fv_stream = (long long)r.ne[0] * (r.storage == CDUGKS_STORE_F64 ? 8 : 4) % 64 == 0;
     P.value_slices = value_slices(r);
     P.close_lanes = close_lanes(r, r.NE * r.D);
     P.has_accel = r.has_accel ? 1 : 0;

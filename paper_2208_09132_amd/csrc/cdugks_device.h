@@ -71,6 +71,38 @@ __device__ __forceinline__ void st_stream(void* base, long long idx, double v) {
     __builtin_nontemporal_store((ST)v, reinterpret_cast<ST*>(base) + idx);
 }
 
+// Face-value stores, NF values fstride apart.  A streaming (non-temporal) store
+// of part of a 64-byte sector is written out as it is, and the memory reads,
+// merges and writes the sector again, while an ordinary one meets the
+// neighbouring tile's part in L2.  So rows of the face grid that do not start
+// on whole sectors (P.fv_stream = 0) take ordinary stores: streaming against
+// ordinary, face sums: 191^2 x 21^2 FP64 441 / 273 us, 310^2 x 18^2 FP32 551 /
+// 377 us, 41^3 x 10^3 FP32 2.81 / 1.38 ms.  On whole sectors streaming wins in
+// FP64, as the update then finds g and b in L2 (256^2 x 28^2, both phases: 1348
+// / 1385 us); in FP32, whose 16-wide tile rows are one sector, it does not (896
+// / 885 us).
+enum { FV_STREAM = 0, FV_ORDINARY = 1, FV_EITHER = 2 };
+// What a face-sum kernel takes unless told otherwise: 1-D tiles are rows of
+// whole lines; a test per store (EITHER) costs the 2-D kernels 2%, the 3-D ones
+// nothing.
+template <int D>
+constexpr int fv_store_mode() { return D == 1 ? FV_STREAM : (D == 2 ? FV_ORDINARY : FV_EITHER); }
+template <typename ST, int NF, int MODE>
+__device__ __forceinline__ void st_faces(const Problem& P, long long o, long long fstride, const ST (&v)[NF]) {
+    ST* const p = (ST*)P.FV + o;
+    if (MODE == FV_STREAM || (MODE == FV_EITHER && P.fv_stream)) {  // uniform
+        // an (empty) difference between the branches, before and after: alike
+        // but for the streaming mark they would be merged into one without it
+        if constexpr (MODE == FV_EITHER) asm volatile("; streaming");
+#pragma unroll
+        for (int k = 0; k < NF; ++k) __builtin_nontemporal_store(v[k], p + k * fstride);
+        if constexpr (MODE == FV_EITHER) asm volatile("; streaming");
+    } else {
+#pragma unroll
+        for (int k = 0; k < NF; ++k) p[k * fstride] = v[k];
+    }
+}
+
 __device__ __forceinline__ void raise_error(int* err) { *err = 1; }
 
 // ---------------------------------------------------------------------------
@@ -610,7 +642,9 @@ struct GaussWalk {
 // terms; the a = 0 instantiations keep their register budget).
 // SUMS: the thread accumulates its faces' velocity sums over the slice;
 // without, it stores the face values only (k_face_reduce sums them).
-template <int D, typename ST, bool DIR = false, bool SS = false, int TID = 0, bool ACC = false, bool SUMS = true>
+// SM: how the face values are stored (st_faces).
+template <int D, typename ST, bool DIR = false, bool SS = false, int TID = 0, bool ACC = false, bool SUMS = true,
+          int SM = fv_store_mode<D>()>
 struct FaceSumKernel {
     using G = Geo<D, TID>;
     static constexpr int NT = G::NT;
@@ -964,8 +998,7 @@ struct FaceSumKernel {
                     // wait for it before using the next velocity's loads
                     const long long o =
                         (long long)(2 * d) * fstride + (long long)i * P.fv_pitch + (fvalid[d] ? fe : NE);
-                    st_stream<CT>(P.FV, o, vg);
-                    st_stream<CT>(P.FV, o + fstride, vb2);
+                    st_faces<CT, 2, SM>(P, o, fstride, fv);
                 }
                 if constexpr (SUMS) {
                     // weighted velocity products come from the table (uniform)
@@ -1355,9 +1388,9 @@ template <int D>
 constexpr int face_sum_waves() { return D == 1 ? 4 : (D == 2 ? 3 : 1); }
 
 // The single-problem face-sum kernel of tile shape TID.
-template <int D, typename ST, bool DIR, bool SS, int TID, bool ACC, bool SUMS = true>
+template <int D, typename ST, bool DIR, bool SS, int TID, bool ACC, bool SUMS = true, int SM = fv_store_mode<D>()>
 __global__ __launch_bounds__(tile_threads(D, TID), face_sum_waves<D>()) void k_face_sums(Problem P) {
-    using K = FaceSumKernel<D, ST, DIR, SS, TID, ACC, SUMS>;
+    using K = FaceSumKernel<D, ST, DIR, SS, TID, ACC, SUMS, SM>;
     static_assert(sizeof(typename K::Smem) == face_sum_lds_bytes(D, TID, sizeof(typename K::CT)),
                   "host and kernel LDS sizes differ");
     __shared__ typename K::Smem sm;
@@ -1453,6 +1486,13 @@ hipError_t launch_face_sums_shape(const Problem& P, hipStream_t s) {
                 hipError_t e = hipGetLastError();
                 if (e != hipSuccess) return e;
                 return launch_face_reduce<D, typename StoreT<ST>::C>(P, s);
+            }
+        }
+        if constexpr (D == 2 && std::is_same<ST, double>::value) {
+            if (P.fv_stream) {
+                hipLaunchKernelGGL((k_face_sums<D, ST, DIR, SS, TID, ACC, true, FV_STREAM>), dim3(nt * P.nslices),
+                                   dim3(tile_threads(D, TID)), 0, s, P);
+                return hipGetLastError();
             }
         }
         hipLaunchKernelGGL((k_face_sums<D, ST, DIR, SS, TID, ACC>), dim3(nt * P.nslices), dim3(tile_threads(D, TID)), 0,
@@ -1692,8 +1732,7 @@ struct ZMarch {
                         // element NE (the store stays unconditional)
                         const long long o = (long long)(2 * d + f0) * fstride + (long long)i * P.fv_pitch +
                                             (valid ? fe : P.NE);
-#pragma unroll
-                        for (int j = 0; j < FL; ++j) st_stream<CT>(P.FV, o + j * fstride, fv[j]);
+                        st_faces<CT, FL, FV_EITHER>(P, o, fstride, fv);
                     }
                 }
             }

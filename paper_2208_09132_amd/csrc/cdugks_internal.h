@@ -84,6 +84,7 @@ struct Problem {
     // a BF16 row; null otherwise
     const long long* rows;
     int recon;    // 0: slopes of slopes (Sec. 2.1), 1: single slope
+    int fv_stream;  // face values are stored with streaming stores (see st_faces)
     int value_slices;  // > 0: face values in this many velocity slices, summed by a second launch
     int tile;     // face-sum tile shape (index into tile_shape(D, .))
     int close_lanes;  // threads per face of the face closure: 1, 16, 64 or 256 (= WG)
