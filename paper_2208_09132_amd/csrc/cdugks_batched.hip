@@ -15,10 +15,12 @@ constexpr int batched_face_waves() { return MAXD <= 2 && !std::is_same<ST, doubl
 template <typename ST, int MAXD, bool DIR, bool SS, bool ACC>
 __global__ __launch_bounds__(WG, (batched_face_waves<ST, MAXD>())) void k_face_sums_batched(const Problem* probs, const WorkItem* items, int nitems,
                                                           int* queue, int* other) {
-    // 2-D problems in the batched tile shape of the storage form
-    constexpr int T2 = MAXD >= 2 ? batched_face_tile(2, std::is_same<ST, double>::value ? 0 : 1) : 0;
+    // Tile shape 0 for every problem.  (32 x 8 tiles were faster in FP32 while
+    // face values were streamed in half lines; with ordinary stores, see
+    // st_faces, 16 x 16 takes 2.05 against 2.11 ms per step of 20 uneven
+    // problems, as fewer cells of the small ones are padding.)
     using K1 = FaceSumKernel<1, ST, DIR, SS, 0, ACC>;
-    using K2 = FaceSumKernel<MAXD >= 2 ? 2 : 1, ST, DIR, SS, T2, ACC>;
+    using K2 = FaceSumKernel<MAXD >= 2 ? 2 : 1, ST, DIR, SS, 0, ACC>;
     using K3 = FaceSumKernel<MAXD >= 3 ? 3 : 1, ST, DIR, SS>;
     __shared__ union U {
         typename K1::Smem s1;

@@ -198,9 +198,9 @@ void batch_free(cdugks_batch* b) {
     delete b;
 }
 
-// Tiles along axis d of a problem in the batched tile shape.
+// Tiles along axis d of a problem in the batched tile shape (0).
 int batched_tiles(const Resolved& r, int d) {
-    const TileExt t = tile_shape(r.D, batched_face_tile(r.D, r.storage));
+    const TileExt t = tile_shape(r.D, 0);
     const int te[3] = {t.x, t.y, t.z};
     return (r.ne[d] + te[d] - 1) / te[d];
 }
@@ -272,7 +272,7 @@ int batch_build(cdugks_ctx* const* ctxs, int count, int chunk_steps, cdugks_batc
             set_pingpong(P, c->r, c->base, c->cur ^ p);
             // batched launches run the batched tile shape of the problem's
             // dimension and storage form (the same result as any other shape)
-            P.tile = batched_face_tile(c->r.D, c->r.storage);
+            P.tile = 0;
             for (int d = 0; d < 3; ++d) P.tiles1[d] = batched_tiles(c->r, d);
             P.close_lanes = lanes;
             P.value_slices = 0;  // a batch fills the device with the slices of the sums
