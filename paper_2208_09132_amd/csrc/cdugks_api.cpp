@@ -664,6 +664,12 @@ int init_context(const cdugks_space* space, const cdugks_velocity* vel, const cd
     for (long long k = 0; k < (long long)r.D * r.N; ++k)
         if (!std::isfinite(u[k])) return fail(CDUGKS_ERR_INVALID, "u[%lld] is not finite", k);
 
+    // kernels reach into a velocity row by 32-bit byte offsets; the
+    // coefficients and face sums of rows past 4 GB (over 300 bytes per cell)
+    // exceed any device's memory
+    if ((unsigned long long)(r.NE + 1) * (r.storage == CDUGKS_STORE_F64 ? 8 : 4) >= (1ULL << 32))
+        return fail(CDUGKS_ERR_NOMEM, "velocity rows of %lld faces do not fit device memory", (long long)r.NE);
+
     cdugks_ctx* c = new (std::nothrow) cdugks_ctx();
     if (!c) return fail(CDUGKS_ERR_NOMEM, "host allocation failed");
     c->r = r;

@@ -255,34 +255,60 @@ __device__ __forceinline__ double slot_value(typename StoreT<ST>::R r, bool half
 // Stores are non-temporal (the kernel never reads them back); round() gives
 // the value as it will be stored.
 struct Bf16Row {};
+// A 32-bit offset that the compiler takes as new at this point.  An address
+// formed from a uniform row and a 32-bit offset costs no VALU instruction, but
+// only where the widening to 64 bits stands beside the access: of an offset
+// that is constant over a loop it would be moved out, leaving a 64-bit sum per
+// access inside.
+__device__ __forceinline__ void keep_offset(unsigned& b) {
+#ifdef __HIP_DEVICE_COMPILE__
+    asm("" : "+v"(b));
+#else
+    (void)b;
+#endif
+}
+// the element `b` bytes into a row (a uniform base)
+template <typename E>
+__device__ __forceinline__ E at_byte(const E* row, unsigned b) {
+    return *(const E*)((const char*)row + b);
+}
 template <typename E>
 struct RowIO {
     using Raw = E;  // a loaded element, as held until used
+    static constexpr int BYTES = sizeof(E);
+    // element c of the row, or (raw_at, st_at) the one b bytes into it
     __device__ static Raw raw(const void* base, long long off, long long c) {
         return ((const E*)((const char*)base + off))[c];
     }
-    __device__ static double val(Raw r) { return (double)r; }
-    __device__ static double ld(const void* base, long long off, long long c) {
-        return (double)((const E*)((const char*)base + off))[c];
+    __device__ static Raw raw_at(const void* base, long long off, unsigned b) {
+        return at_byte((const E*)((const char*)base + off), b);
     }
+    __device__ static double val(Raw r) { return (double)r; }
     __device__ static void st(void* base, long long off, long long c, double v) {
         __builtin_nontemporal_store((E)v, (E*)((char*)base + off) + c);
+    }
+    __device__ static void st_at(void* base, long long off, unsigned b, double v) {
+        __builtin_nontemporal_store((E)v, (E*)((char*)base + off + b));
     }
     __device__ static double round(double v) { return (double)(E)v; }
 };
 template <>
 struct RowIO<Bf16Row> {
     using Raw = __bf16;
+    static constexpr int BYTES = 2;
     __device__ static Raw raw(const void* base, long long off, long long c) {
         return ((const __bf16*)((const char*)base + off))[c];
     }
-    __device__ static double val(Raw r) { return (double)(float)r; }
-    __device__ static double ld(const void* base, long long off, long long c) {
-        return (double)(float)((const __bf16*)((const char*)base + off))[c];
+    __device__ static Raw raw_at(const void* base, long long off, unsigned b) {
+        return at_byte((const __bf16*)((const char*)base + off), b);
     }
+    __device__ static double val(Raw r) { return (double)(float)r; }
     __device__ static void st(void* base, long long off, long long c, double v) {
+        st_at(base, off + 2 * c, 0, v);
+    }
+    __device__ static void st_at(void* base, long long off, unsigned b, double v) {
         const unsigned short h = __builtin_bit_cast(unsigned short, (__bf16)(float)v);
-        __builtin_nontemporal_store(h, (unsigned short*)((char*)base + off) + c);
+        __builtin_nontemporal_store(h, (unsigned short*)((char*)base + off + b));
     }
     __device__ static double round(double v) { return (double)(float)(__bf16)(float)v; }
 };
@@ -598,7 +624,7 @@ __device__ __forceinline__ double maxwellian_f32(double A, double s, const doubl
 // expanded square (relative 1e-16 of |xi|^2 + |u|^2) stays far below the
 // FP32 accuracy of the result.
 __device__ __forceinline__ double maxwellian_f32z(double A, double s, double Z, double hx2) {
-    const double t = fmin(fmax(2.0 * M_LOG2E * s * (Z - hx2), -1500.0), 1500.0);
+    const double t = fmax(2.0 * M_LOG2E * s * (Z - hx2), -1500.0);  // at most rounding above 0
     const double n = rint(t);
     return A * ldexp((double)__builtin_amdgcn_exp2f((float)(t - n)), (int)n);
 }
@@ -1147,6 +1173,34 @@ struct UpdateKernel {
         const long long cc = inside ? c : 0;
         unsigned fl[D], fr[D];
         cell_faces<D>(P, (unsigned)cc, fl, fr);
+        // Byte offsets of the cell and its faces in their rows: 32 bits reach
+        // any row the device's memory can hold (checked at set-up), and a
+        // uniform row plus a 32-bit offset is an address the loads and stores
+        // form themselves, where 64-bit sums took 12 (2-D) and 18 (3-D) VALU
+        // instructions per velocity.  A cell's left faces share one index.
+        // (One set for g, one for b: of a shared one the sum with g's row would
+        // be shared too, in 64 bits.)  Update of 64^3 x 16^3 FP32 13.9 -> 12.4
+        // ms, 256^2 x 28^2 FP64 637 -> 629 us; the 2-D FP32 forms, which wait
+        // for the rows' scalar arithmetic instead, lose (357 -> 372 us, batches
+        // 5%) and keep the 64-bit sums.
+        constexpr bool ROW32 = D != 2 || std::is_same<ST, double>::value;
+        unsigned oc = (unsigned)cc, bl[2], br[2][D];
+#pragma unroll
+        for (int f = 0; f < 2; ++f) {
+            bl[f] = fl[0] * (unsigned)sizeof(CT);
+#pragma unroll
+            for (int d = 0; d < D; ++d) br[f][d] = fr[d] * (unsigned)sizeof(CT);
+        }
+        auto store = [&](auto kind, void* base, long long off, double v) __attribute__((always_inline)) {
+            using IO = RowIO<decltype(kind)>;
+            if constexpr (ROW32) {
+                unsigned ob = oc * (unsigned)IO::BYTES;
+                keep_offset(ob);
+                IO::st_at(base, off, ob, v);
+            } else {
+                IO::st(base, off, cc, v);
+            }
+        };
         const CellCoef k0 = load_coef(P.P_in, N, cc);
         CellCoef k1;
         if constexpr (CLOSE) k1 = cell_close<D>(P, cc, fl, fr, inside && slice == 0 && ROWS != 2);
@@ -1209,16 +1263,37 @@ struct UpdateKernel {
         auto load = [&](int i, long long off, auto kind, typename RowIO<decltype(kind)>::Raw& rg,
                         typename RowIO<decltype(kind)>::Raw& rb, CT (&fv)[4 * D]) __attribute__((always_inline)) {
             using IO = RowIO<decltype(kind)>;
-            rg = IO::raw(P.g_in, off, cc);
-            rb = IO::raw(P.b_in, off, cc);
+            if constexpr (ROW32) {
+                unsigned ob = oc * (unsigned)IO::BYTES;
+                keep_offset(ob);
+#pragma unroll
+                for (int f = 0; f < 2; ++f) {
+                    keep_offset(bl[f]);
+#pragma unroll
+                    for (int d = 0; d < D; ++d) keep_offset(br[f][d]);
+                }
+                rg = IO::raw_at(P.g_in, off, ob);
+                rb = IO::raw_at(P.b_in, off, ob);
+            } else {
+                rg = IO::raw(P.g_in, off, cc);
+                rb = IO::raw(P.b_in, off, cc);
+            }
             const CT* const F = (const CT*)P.FV;
 #pragma unroll
             for (int d = 0; d < D; ++d) {
-                const long long o = (long long)(2 * d) * fstride + (long long)i * P.fv_pitch;
-                fv[4 * d] = F[o + fl[d]];
-                fv[4 * d + 1] = F[o + fstride + fl[d]];
-                fv[4 * d + 2] = F[o + fr[d]];
-                fv[4 * d + 3] = F[o + fstride + fr[d]];
+                const CT* const rowg = F + ((long long)(2 * d) * fstride + (long long)i * P.fv_pitch);
+                const CT* const rowb = rowg + fstride;
+                if constexpr (ROW32) {
+                    fv[4 * d] = at_byte(rowg, bl[0]);
+                    fv[4 * d + 1] = at_byte(rowb, bl[1]);
+                    fv[4 * d + 2] = at_byte(rowg, br[0][d]);
+                    fv[4 * d + 3] = at_byte(rowb, br[1][d]);
+                } else {
+                    fv[4 * d] = rowg[fl[d]];
+                    fv[4 * d + 1] = rowb[fl[d]];
+                    fv[4 * d + 2] = rowg[fr[d]];
+                    fv[4 * d + 3] = rowb[fr[d]];
+                }
             }
         };
         // One velocity of the slice from its loads; its rows (g, b in and
@@ -1301,14 +1376,14 @@ struct UpdateKernel {
             gn *= inv_g;
             bn *= inv_b;
             if (inside) {
-                IO::st(P.g_out, off, cc, gn);
-                IO::st(P.b_out, off, cc, bn);
+                store(kind, P.g_out, off, gn);
+                store(kind, P.b_out, off, bn);
                 if constexpr (quarter_stored(D)) {
                     // next step's phi_bar_plus from the state as stored
                     double qg, qb;
                     quarter_step_eq<D, ACC>(k1, v, geq1, IO::round(gn), IO::round(bn), qg, qb, &P);
-                    IO::st(P.qg, off, cc, qg);
-                    IO::st(P.qb, off, cc, qb);
+                    store(kind, P.qg, off, qg);
+                    store(kind, P.qb, off, qb);
                 }
             }
             if constexpr (WALKER) {
@@ -1332,6 +1407,10 @@ struct UpdateKernel {
                 typename RowIO<ST>::Raw rg, rb;
                 CT fv[4 * D];
                 load(i, off_of(i), ST{}, rg, rb, fv);
+                // every load before any of the arithmetic (3-D FP64; left to
+                // itself the compiler sinks some, 690 -> 661 us on 37 x 29 x 23
+                // cells x 11 x 10 x 12; FP32 gains nothing)
+                if constexpr (std::is_same<ST, double>::value) __builtin_amdgcn_sched_barrier(1);
                 velocity(i, off_of(i), ST{}, rg, rb, fv);
             }
         } else if constexpr (!StoreT<ST>::MIXED) {
