@@ -71,6 +71,23 @@ __device__ __forceinline__ void st_stream(void* base, long long idx, double v) {
     __builtin_nontemporal_store((ST)v, reinterpret_cast<ST*>(base) + idx);
 }
 
+// A 32-bit offset that the compiler takes as new at this point.  An address
+// formed from a uniform row and a 32-bit offset costs no VALU instruction, but
+// only where the widening to 64 bits stands beside the access: of an offset
+// that is constant over a loop it would be moved out, leaving a 64-bit sum per
+// access inside.
+__device__ __forceinline__ void keep_offset(unsigned& b) {
+#ifdef __HIP_DEVICE_COMPILE__
+    asm("" : "+v"(b));
+#else
+    (void)b;
+#endif
+}
+// the element `b` bytes into a row (a uniform base)
+template <typename E>
+__device__ __forceinline__ E at_byte(const E* row, unsigned b) {
+    return *(const E*)((const char*)row + b);
+}
 // Face-value stores, NF values fstride apart.  A streaming (non-temporal) store
 // of part of a 64-byte sector is written out as it is, and the memory reads,
 // merges and writes the sector again, while an ordinary one meets the
@@ -87,6 +104,31 @@ enum { FV_STREAM = 0, FV_ORDINARY = 1, FV_EITHER = 2 };
 // nothing.
 template <int D>
 constexpr int fv_store_mode() { return D == 1 ? FV_STREAM : (D == 2 ? FV_ORDINARY : FV_EITHER); }
+// row: the value's row (uniform), b: its byte offset there, 32 bits as in the
+// update: with 64-bit sums per load and store the z-march, bound by VALU issue,
+// took 4 to 5 registers more and 32^3 FP32 cells 1009 us for the face sums
+// instead of 987, 37 x 29 x 23 cells 743 instead of 695 (FP64 storage 1396
+// instead of 1379)
+template <typename ST, int NF, int MODE>
+__device__ __forceinline__ void st_faces_row(const Problem& P, ST* row, unsigned b, long long fstride,
+                                             const ST (&v)[NF]) {
+    unsigned bk[NF];
+#pragma unroll
+    for (int k = 0; k < NF; ++k) {
+        bk[k] = b;
+        keep_offset(bk[k]);
+    }
+    auto at = [&](int k) __attribute__((always_inline)) { return (ST*)((char*)(row + k * fstride) + bk[k]); };
+    if (MODE == FV_STREAM || (MODE == FV_EITHER && P.fv_stream)) {  // uniform
+        if constexpr (MODE == FV_EITHER) asm volatile("; streaming");
+#pragma unroll
+        for (int k = 0; k < NF; ++k) __builtin_nontemporal_store(v[k], at(k));
+        if constexpr (MODE == FV_EITHER) asm volatile("; streaming");
+    } else {
+#pragma unroll
+        for (int k = 0; k < NF; ++k) *at(k) = v[k];
+    }
+}
 template <typename ST, int NF, int MODE>
 __device__ __forceinline__ void st_faces(const Problem& P, long long o, long long fstride, const ST (&v)[NF]) {
     ST* const p = (ST*)P.FV + o;
@@ -255,23 +297,6 @@ __device__ __forceinline__ double slot_value(typename StoreT<ST>::R r, bool half
 // Stores are non-temporal (the kernel never reads them back); round() gives
 // the value as it will be stored.
 struct Bf16Row {};
-// A 32-bit offset that the compiler takes as new at this point.  An address
-// formed from a uniform row and a 32-bit offset costs no VALU instruction, but
-// only where the widening to 64 bits stands beside the access: of an offset
-// that is constant over a loop it would be moved out, leaving a 64-bit sum per
-// access inside.
-__device__ __forceinline__ void keep_offset(unsigned& b) {
-#ifdef __HIP_DEVICE_COMPILE__
-    asm("" : "+v"(b));
-#else
-    (void)b;
-#endif
-}
-// the element `b` bytes into a row (a uniform base)
-template <typename E>
-__device__ __forceinline__ E at_byte(const E* row, unsigned b) {
-    return *(const E*)((const char*)row + b);
-}
 template <typename E>
 struct RowIO {
     using Raw = E;  // a loaded element, as held until used
@@ -1652,7 +1677,7 @@ struct ZMarch {
         // q-plane points of this thread: in-plane source offset after the
         // periodic wrap / outflow clamp, and for Dirichlet sides the side of
         // the point's x or y coordinate (2 d + side + 1, y over x, 0: none)
-        long long off[NSLOT];
+        unsigned off[NSLOT];
         int lq[NSLOT];
         int sxy[DIR ? NSLOT : 1];
 #pragma unroll
@@ -1661,7 +1686,7 @@ struct ZMarch {
             lq[k] = p < NQ ? p : -1;
             const int pp = p < NQ ? p : 0;
             const int x = ox + pp % QX - 3, y = oy + pp / QX - 3;
-            off[k] = map_coord(x, n0, P.bc[0]) + (long long)n0 * map_coord(y, n1, P.bc[1]);
+            off[k] = (unsigned)map_coord(x, n0, P.bc[0]) + (unsigned)n0 * (unsigned)map_coord(y, n1, P.bc[1]);
             if constexpr (DIR) {
                 int side = 0;
                 if (P.bc[0] == 2 && (x < 0 || x >= n0)) side = (x >= n0) + 1;
@@ -1676,15 +1701,22 @@ struct ZMarch {
         RT pg[NSLOT], pb[NSLOT];
         auto load_plane = [&](int z) __attribute__((always_inline)) {
             const long long base = (long long)map_coord(z, n2, P.bc[2]) * nplane;
-            long long src[NSLOT];
+            if constexpr (StoreT<ST>::MIXED) {
+                long long src[NSLOT];
 #pragma unroll
-            for (int k = 0; k < NSLOT; ++k) src[k] = base + off[k];
-            if constexpr (NF == 1) {
+                for (int k = 0; k < NSLOT; ++k) src[k] = base + off[k];
                 load_slots<ST, NSLOT, false>(P, P.qg, P.qb, i, src, pg, pb);
             } else {
-                const void* const q = f0 ? P.qb : P.qg;
+                // the plane's start is uniform, a point's offset in it 32 bits
+                const ST* const rg = (const ST*)(f0 ? P.qb : P.qg) + ((long long)i * P.pitch + base);
+                const ST* const rb = (const ST*)P.qb + ((long long)i * P.pitch + base);
 #pragma unroll
-                for (int k = 0; k < NSLOT; ++k) pg[k] = state_load<ST>(P, q, i, src[k]);
+                for (int k = 0; k < NSLOT; ++k) {
+                    unsigned o = off[k] * (unsigned)sizeof(ST);
+                    keep_offset(o);
+                    pg[k] = at_byte(rg, o);
+                    if constexpr (NF == 1) pb[k] = at_byte(rb, o);
+                }
             }
         };
         auto store_plane = [&](int z) __attribute__((always_inline)) {
@@ -1731,8 +1763,8 @@ struct ZMarch {
         const int tx = ct % TX, ty = ct / TX;
         const int gx = ox + tx, gy = oy + ty;
         const bool vx = gx < P.ne[0] && gy < n1, vy = gx < n0 && gy < P.ne[1], vz = gx < n0 && gy < n1;
-        const long long fplane = (long long)P.ne[0] * P.ne[1];
-        const long long fe0 = gx + (long long)P.ne[0] * gy;
+        const unsigned fplane = (unsigned)P.ne[0] * (unsigned)P.ne[1], spare = (unsigned)P.NE;
+        const unsigned fe0 = (unsigned)gx + (unsigned)P.ne[0] * (unsigned)gy;
         const long long fstride = P.fv_stride;
         const int qo_i = qidx(tx, ty), ao_i = aidx(tx, ty);
 
@@ -1749,7 +1781,7 @@ struct ZMarch {
                 for (int e = 0; e < 3; ++e) ao[j][e] = sm.a[ra][f0 + j][e][ao_i];
             }
             if (emit) {
-                const long long fe = fe0 + fplane * z;
+                const unsigned fe = fe0 + fplane * (unsigned)z;  // 32 bits hold a row (checked at set-up)
 #pragma unroll
                 for (int d = 0; d < 3; ++d) {
                     const bool valid = d == 0 ? (vx && z < n2) : (d == 1 ? (vy && z < n2) : vz);
@@ -1809,9 +1841,9 @@ struct ZMarch {
                     {
                         // a face outside the grid goes to the row's spare
                         // element NE (the store stays unconditional)
-                        const long long o = (long long)(2 * d + f0) * fstride + (long long)i * P.fv_pitch +
-                                            (valid ? fe : P.NE);
-                        st_faces<CT, FL, FV_EITHER>(P, o, fstride, fv);
+                        CT* const row = (CT*)P.FV + ((long long)(2 * d + f0) * fstride + (long long)i * P.fv_pitch);
+                        st_faces_row<CT, FL, FV_EITHER>(P, row, (valid ? fe : spare) * (unsigned)sizeof(CT), fstride,
+                                                        fv);
                     }
                 }
             }
