@@ -132,6 +132,9 @@ typedef struct {
                                  dim 2: 16x16, 32x8, 8x32, 32x24
                                  dim 3: 16x4x4, 32x4x2, 64x2x2, 32x6x4, 64x4x3, 16x8x6,
                                         16x16xZ, 32x8xZ, 32x16xZ
+                               (the 16x16 column takes up to 256 cells in other
+                               proportions where the grid's x and y extents cut
+                               it; the results are the same)
                                (xZ: a column that walks the whole z extent for
                                one velocity, storing the face values, followed by
                                a kernel that sums them over velocities).  The

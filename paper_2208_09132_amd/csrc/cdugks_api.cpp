@@ -321,11 +321,53 @@ int resolve(const cdugks_space* sp, const cdugks_velocity* ve, const cdugks_para
     return CDUGKS_OK;
 }
 
+// The cells of the z-marching column that a face grid runs with under the
+// 16 x 16 shape, which stays (0, 0) where no other is estimated 10% cheaper.
+// The estimate counts VALU instructions per plane, which bound the kernel: a
+// column's faces (210 per wave), limited differences (29) and staged points
+// (12), and for its rows one per value stored and a 64-byte sector's values
+// per cut of a row.  Fewer waves than 4 per field save hardly anything: 3 (6
+// in FP64) spread unevenly over a CU's 4 SIMDs (37 x 29 x 23, 6 columns of
+// 16 x 16 or 19 x 10: FP64 1419 and 1376 us, FP32 723 and 677; 5 of 8 x 29:
+// 1286 and 734).  Face sums with and without the rule: 20^3 x 12^3 FP64 887
+// and 578 us, FP32 461 and 317; 33 x 33 x 20 x 10^3 FP64 1232 and 989; 30
+// drawn sizes, FP64 and FP32, 0.63 to 1.0 of the time, 0.90 on average.  Grids
+// in whole sectors (streaming stores) take columns of whole sectors.
+static void choose_column(const Resolved& r, int (&column)[2]) {
+    const int es = r.storage == CDUGKS_STORE_F64 ? 8 : 4, nf = es == 8 ? 2 : 1;
+    auto waves = [](int n) { return (n + 63) / 64; };
+    auto cost = [&](int x, int y, int cells) {
+        const long long cx = (r.ne[0] + x - 1) / x, cy = (r.ne[1] + y - 1) / y;
+        const int faces = nf == 1 && cells == 192 ? 800 : 840;
+        return cx * cy * (faces + 29 * waves(2 * (x + 3) * (y + 3)) + 12 * waves((x + 5) * (y + 5))) +
+               r.ne[1] * (r.ne[0] + cx * (64 / es));
+    };
+    column[0] = column[1] = 0;
+    const bool rows64 = (long long)r.ne[0] * es % 64 == 0;
+    long long best = cost(16, 16, 256) * 9 / 10;
+    for (int x = 64; x >= 4; --x) {
+        if (rows64 && x * es % 64 != 0) continue;
+        for (int y = 1; x * y <= 256; ++y) {
+            const int cells = column_fits(x, y, nf, 192) ? 192 : 256;
+            if (!column_fits(x, y, nf, cells)) continue;
+            if (const long long c = cost(x, y, cells); c < best) {
+                best = c;
+                column[0] = x;
+                column[1] = y;
+            }
+        }
+    }
+}
+
 void set_face_tile(Resolved& r, int tile) {
     const TileExt t = tile_shape(r.D, tile);
     // a z-marching column spans the face grid along z
-    const int te[3] = {t.x, t.y, tile_zmarch(r.D, tile) ? r.ne[2] : t.z};
+    int te[3] = {t.x, t.y, tile_zmarch(r.D, tile) ? r.ne[2] : t.z};
     r.tile = tile;
+    r.column[0] = r.column[1] = 0;
+    if (tile_zmarch(r.D, tile) && tile == default_face_tile(r.D)) choose_column(r, r.column);
+    if (r.column[0] > 0)
+        for (int d = 0; d < 2; ++d) te[d] = r.column[d];
     for (int d = 0; d < 3; ++d) r.tiles1[d] = (r.ne[d] + te[d] - 1) / te[d];
 }
 
@@ -512,6 +554,7 @@ void fill_problem(const Resolved& r, char* base, Problem& P) {
         P.bc[d] = r.bc[d];
         P.nv[d] = r.nv[d];
         P.tiles1[d] = r.tiles1[d];
+        if (d < 2) P.column[d] = r.column[d];
         P.dx[d] = r.dx[d];
         P.inv_dx[d] = 1.0 / r.dx[d];
     }

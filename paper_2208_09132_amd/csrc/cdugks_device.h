@@ -1647,31 +1647,44 @@ int face_sum_occupancy_shape() {
 template <typename CT>
 constexpr int zmarch_threads_per_cell() { return sizeof(CT) == 8 ? 2 : 1; }
 
+// TX = 0: the column is P.column[0] x P.column[1] cells, up to TY of them,
+// chosen for the problem's extents within the bounds of column_fits, and the
+// workgroup one wave per 64 cells and thread of a cell.  (Against 16 x 16
+// columns of the same number: 48 x 40 x 24 FP64 1695 and 1683 us.)
 template <typename ST, bool DIR, bool SS, int TX, int TY>
 struct ZMarch {
     using CT = typename StoreT<ST>::C;
     using RT = typename StoreT<ST>::R;
-    static constexpr int NT = TX * TY;                        // cells of the column
+    static constexpr bool FIXED = TX > 0;
+    static constexpr int NT = FIXED ? TX * TY : TY;           // cells of the column (at most)
     static constexpr int NF = zmarch_threads_per_cell<CT>();  // threads per cell
-    static constexpr int NTH = NF * NT;                       // threads of the workgroup
+    static constexpr int NTH = NF * NT;                       // threads of the workgroup (at most)
     static constexpr int FL = 2 / NF;                         // fields per thread
-    static constexpr int QX = TX + 5, QY = TY + 5, NQ = QX * QY;  // q plane
-    static constexpr int AX = TX + 3, AY = TY + 3, NA = AX * AY;  // difference plane
-    static constexpr int NSLOT = (NQ + NT - 1) / NT;              // q points per thread
-    static constexpr int NPASS = (2 * NA + NTH - 1) / NTH;        // (point, field) passes
+    // points of a q plane and of a difference plane (at most)
+    static constexpr int NQ = FIXED ? (TX + 5) * (TY + 5) : column_nq(TY);
+    static constexpr int NA = FIXED ? (TX + 3) * (TY + 3) : column_na(TY);
+    static constexpr int NSLOT = FIXED ? (NQ + NT - 1) / NT : COLUMN_SLOTS;  // q points per thread
+    // (point, field) passes
+    static constexpr int NPASS = FIXED ? (2 * NA + NTH - 1) / NTH : column_passes(NF);
     static_assert(NF == 1 || !StoreT<ST>::MIXED, "the BF16-tail form loads its rows through load_slots");
     struct Smem {
         CT q[4][2][NQ];
         CT a[2][2][3][NA];  // [ring][field][component][point]
     };
-    __device__ static int qidx(int x, int y) { return (x + 3) + QX * (y + 3); }
-    __device__ static int aidx(int x, int y) { return (x + 2) + AX * (y + 2); }
 
     __device__ static void run(const Problem& P, int tile, int i, Smem& sm) {
+        const int tx0 = FIXED ? TX : P.column[0], ty0 = FIXED ? TY : P.column[1];
+        const int QX = tx0 + 5, nq = QX * (ty0 + 5);
+        const int AX = tx0 + 3, na = AX * (ty0 + 3);
+        const int nth = FIXED ? NTH : (int)blockDim.x;
+        const int nt = FIXED ? NT : nth / NF;  // threads per field, whole waves
+        auto qidx = [&](int x, int y) __attribute__((always_inline)) { return (x + 3) + QX * (y + 3); };
+        auto aidx = [&](int x, int y) __attribute__((always_inline)) { return (x + 2) + AX * (y + 2); };
         const int tid = threadIdx.x;
-        const int ct = tid % NT;           // cell of the column
-        const int f0 = NF == 2 ? tid / NT : 0;  // first field of the thread (uniform per wave)
-        const int ox = (tile % P.tiles1[0]) * TX, oy = (tile / P.tiles1[0]) * TY;
+        // first field of the thread (uniform per wave) and cell of the column
+        const int f0 = NF == 2 ? (FIXED ? tid / NT : tid >= nt) : 0;
+        const int ct = FIXED ? tid % NT : tid - f0 * nt;
+        const int ox = (tile % P.tiles1[0]) * tx0, oy = (tile / P.tiles1[0]) * ty0;
         const int n0 = P.n[0], n1 = P.n[1], n2 = P.n[2];
         const long long nplane = (long long)n0 * n1;
         // q-plane points of this thread: in-plane source offset after the
@@ -1682,9 +1695,9 @@ struct ZMarch {
         int sxy[DIR ? NSLOT : 1];
 #pragma unroll
         for (int k = 0; k < NSLOT; ++k) {
-            const int p = ct + k * NT;
-            lq[k] = p < NQ ? p : -1;
-            const int pp = p < NQ ? p : 0;
+            const int p = ct + k * nt;
+            lq[k] = p < nq ? p : -1;
+            const int pp = p < nq ? p : 0;
             const int x = ox + pp % QX - 3, y = oy + pp / QX - 3;
             off[k] = (unsigned)map_coord(x, n0, P.bc[0]) + (unsigned)n0 * (unsigned)map_coord(y, n1, P.bc[1]);
             if constexpr (DIR) {
@@ -1741,28 +1754,38 @@ struct ZMarch {
             }
         };
         // limited differences of plane z on the difference plane
+        int dq[NPASS], da[NPASS];  // a pass's points in a q plane's and a difference plane's two fields
+#pragma unroll
+        for (int k = 0; k < NPASS; ++k) {
+            const int t = tid + k * nth;
+            const int f = t >= na;
+            const int pt = t - f * na;
+            dq[k] = f * NQ + (pt % AX + 1) + QX * (pt / AX + 1);
+            da[k] = f * 3 * NA + pt;
+        }
         auto differences = [&](int z) __attribute__((always_inline)) {
             const int rm = (z + 7) & 3, r0 = (z + 8) & 3, rp = (z + 9) & 3, ra = (z + 8) & 1;
 #pragma unroll
             for (int k = 0; k < NPASS; ++k) {
-                const int t = tid + k * NTH;
-                if (t < 2 * NA) {
-                    const int f = t >= NA;
-                    const int pt = t - f * NA;
-                    const int qi = (pt % AX + 1) + QX * (pt / AX + 1);
-                    const CT* q = sm.q[r0][f];
-                    const CT c = q[qi];
-                    sm.a[ra][f][0][pt] = half_van_leer(c - q[qi - 1], q[qi + 1] - c);
-                    sm.a[ra][f][1][pt] = half_van_leer(c - q[qi - QX], q[qi + QX] - c);
-                    sm.a[ra][f][2][pt] = half_van_leer(c - sm.q[rm][f][qi], sm.q[rp][f][qi] - c);
+                if (tid + k * nth < 2 * na) {
+                    const CT *q = sm.q[r0][0] + dq[k], *qm = sm.q[rm][0] + dq[k], *qp = sm.q[rp][0] + dq[k];
+                    CT* const a = sm.a[ra][0][0] + da[k];
+                    const CT c = q[0];
+                    a[0] = half_van_leer(c - q[-1], q[1] - c);
+                    a[NA] = half_van_leer(c - q[-QX], q[QX] - c);
+                    a[2 * NA] = half_van_leer(c - qm[0], qp[0] - c);
                 }
             }
         };
 
         // own cell, the validity of its left faces and their face-grid index
-        const int tx = ct % TX, ty = ct / TX;
+        // (a thread past the last cell takes cell 0 and no valid face)
+        const bool own = FIXED || ct < tx0 * ty0;
+        const int cc = own ? ct : 0;
+        const int tx = cc % tx0, ty = cc / tx0;
         const int gx = ox + tx, gy = oy + ty;
-        const bool vx = gx < P.ne[0] && gy < n1, vy = gx < n0 && gy < P.ne[1], vz = gx < n0 && gy < n1;
+        const bool vx = own && gx < P.ne[0] && gy < n1, vy = own && gx < n0 && gy < P.ne[1],
+                   vz = own && gx < n0 && gy < n1;
         const unsigned fplane = (unsigned)P.ne[0] * (unsigned)P.ne[1], spare = (unsigned)P.NE;
         const unsigned fe0 = (unsigned)gx + (unsigned)P.ne[0] * (unsigned)gy;
         const long long fstride = P.fv_stride;
@@ -1900,7 +1923,17 @@ hipError_t launch_face_sums_zmarch(const Problem& P, hipStream_t s) {
                   "host and kernel LDS sizes differ");
     if constexpr (face_tile_fits(3, TID, sizeof(typename K::CT))) {
         const unsigned nb = (unsigned)((long long)P.tiles1[0] * P.tiles1[1] * P.V);
-        hipLaunchKernelGGL((k_face_values_z<ST, DIR, SS, T.x, T.y>), dim3(nb), dim3(K::NTH), 0, s, P);
+        if (P.column[0] > 0) {
+            const dim3 block(K::NF * 64u * ((unsigned)(P.column[0] * P.column[1] + 63) / 64));
+            if (column_fits(P.column[0], P.column[1], K::NF, 192))
+                hipLaunchKernelGGL((k_face_values_z<ST, DIR, SS, 0, 192>), dim3(nb), block, 0, s, P);
+            else if (column_fits(P.column[0], P.column[1], K::NF, 256))
+                hipLaunchKernelGGL((k_face_values_z<ST, DIR, SS, 0, 256>), dim3(nb), block, 0, s, P);
+            else
+                return hipErrorInvalidConfiguration;
+        } else {
+            hipLaunchKernelGGL((k_face_values_z<ST, DIR, SS, T.x, T.y>), dim3(nb), dim3(K::NTH), 0, s, P);
+        }
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
         return launch_face_reduce<3, typename K::CT>(P, s);

@@ -87,6 +87,7 @@ struct Problem {
     int fv_stream;  // face values are stored with streaming stores (see st_faces)
     int value_slices;  // > 0: face values in this many velocity slices, summed by a second launch
     int tile;     // face-sum tile shape (index into tile_shape(D, .))
+    int column[2];  // the z-marching column's cells along x, y where they are not the shape's (0: they are)
     int close_lanes;  // threads per face of the face closure: 1, 16, 64 or 256 (= WG)
     int has_accel;     // external acceleration present (a != 0)
     double accel[3];   // external acceleration a (eqs. gPDE, bPDE)
@@ -212,5 +213,21 @@ constexpr long long face_sum_lds_bytes(int D, int id, int es) {
 }
 constexpr long long LDS_PER_CU = 160 * 1024;
 constexpr bool face_tile_fits(int D, int id, int es) { return face_sum_lds_bytes(D, id, es) <= LDS_PER_CU; }
+
+// Columns of other cells than the 16 x 16 shape's (ZMarch<., 0, cells>), of up
+// to 192 and up to 256 cells: the points of a q plane and of a difference
+// plane that the kernel's LDS holds (so that a CU holds 18 waves of the former
+// and as many workgroups of the latter as of 16 x 16 columns), the q points of
+// a thread and the passes over both fields' differences.
+constexpr int column_nq(int cells) { return cells == 192 ? 390 : 450; }
+constexpr int column_na(int cells) { return cells == 192 ? 308 : 382; }
+constexpr int COLUMN_SLOTS = 2;
+constexpr int column_passes(int nf) { return nf == 2 ? 2 : 3; }
+// nf: threads per cell
+constexpr bool column_fits(int x, int y, int nf, int cells) {
+    const int q = (x + 5) * (y + 5), a = (x + 3) * (y + 3), nt = (x * y + 63) / 64 * 64;
+    return x > 0 && y > 0 && nt <= cells && q <= column_nq(cells) && a <= column_na(cells) &&
+           q <= COLUMN_SLOTS * nt && 2 * a <= column_passes(nf) * nf * nt;
+}
 
 }  // namespace cdg
