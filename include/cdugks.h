@@ -171,7 +171,9 @@ int cdugks_required_bytes(const cdugks_space* space, const cdugks_velocity* vel,
  * rho[N] > 0, u[dim][N], T[N] > 0 are host arrays.  hip_stream is the stream
  * all work of this context is enqueued on.  arena (device pointer, >= the
  * cdugks_required_bytes figure, 256-byte aligned) may be NULL, in which case
- * the library allocates.  Validation failures return CDUGKS_ERR_INVALID:
+ * the library allocates (memory it releases while other contexts or servers
+ * live on the device may stay with it, up to 1/32 of the device's, for the
+ * next; it is given back with the last of them).  Validation failures return CDUGKS_ERR_INVALID:
  * dim outside 1..3, n < 1, nv < 2, Boole with nv != 4k+1, gamma outside
  * (1, 5/3], Pr <= 0, R <= 0, rho <= 0, T <= 0 (in a cell or a Dirichlet
  * state), an unknown boundary condition, a requested dt above the CFL
@@ -270,8 +272,9 @@ int cdugks_info(cdugks_ctx* ctx, double* dt, double* t, int64_t* steps);
 
 /* Timing helper: advance nsteps steps launching every phase on its own, with
  * HIP events recorded between the phases on the context's stream; ms[4]
- * receives the mean duration per step (milliseconds) of the four kernels of a
- * step: face sums, face closure, cell closure, update.  Waits for the stream. */
+ * receives the mean duration per step (milliseconds) of a step's phases: face
+ * sums, face closure, 0 (the cell closure is part of the update), update.
+ * Waits for the stream. */
 int cdugks_profile_phases(cdugks_ctx* ctx, int64_t nsteps, double* ms);
 
 /* Release the context (waits for its stream).  NULL-safe.  A context that

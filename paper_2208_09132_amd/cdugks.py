@@ -350,7 +350,8 @@ class Solver:
 
     def profile_phases(self, nsteps: int):
         """Mean per-step kernel durations (ms) from HIP events on the context's
-        stream: face sums, face closure, cell closure, update."""
+        stream: face sums, face closure, zero (the cell closure is part of
+        the update), update."""
         ms = np.zeros(4)
         check(load_library().cdugks_profile_phases(self.ctx, int(nsteps), _ptr(ms)))
         return ms
