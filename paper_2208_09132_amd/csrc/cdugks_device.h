@@ -41,12 +41,7 @@ __device__ __forceinline__ double rcp_nr(double s) {
 __device__ __forceinline__ double half_van_leer(double a, double b) {
     double p = a * b;
     double v = p * rcp_nr(a + b);
-    // The limit's zero as a zero high word alone: what the low word leaves is
-    // below 3e-314, and the face sums, bound by VALU issue, select 14 words
-    // less per velocity (256^2 x 28^2: 721 -> 702 us).
-    const unsigned long long bits = __builtin_bit_cast(unsigned long long, v);
-    const unsigned hi = p > 0.0 ? (unsigned)(bits >> 32) : 0u;
-    return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | (unsigned)bits);
+    return p > 0.0 ? v : 0.0;
 }
 
 // FP32 form for the FP32-storage stencil: the hardware reciprocal alone
