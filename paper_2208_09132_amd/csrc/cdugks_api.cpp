@@ -528,14 +528,20 @@ int value_slices(const Resolved& r) {
 // Threads per face of the face closure (speed only), of a launch that closes
 // `faces` faces: groups that share a face's nodes, larger ones for longer
 // axes, as long as two workgroups per CU hold them all.  One thread per face
-// where not even the smallest groups have that room, unless a face's nodes are
-// so many that its thread would outlast theirs (16 threads against one: 7.9
-// and 12 us for 64^2 cells x 16^2 velocities, 8192 faces; 27 and 16 us for
-// 96^2 x 20^2; 25 us both for 20000 faces of 129 nodes).
+// where not even the smallest groups have that room (16 threads against one:
+// 7.9 and 12 us for 64^2 cells x 16^2 velocities, 8192 faces; 27 and 16 us for
+// 96^2 x 20^2).  A face of more than 256 nodes keeps a group of 16 beyond
+// that, while its serial sums outlast the groups' rounds: 1-D up to 3 times
+// the room (24000 faces of 257 nodes 42 and 44 us, of 1025 nodes 123 and 170;
+// 32000 of 257 53 and 43), 2-D, where the group's longest sum is half its
+// nodes, up to 2 times (16200 faces of 258 nodes 43 and 46 us, 20000 51 and
+// 45).  With a group at any number of faces, 200000 of 257 nodes took 292 us
+// (one thread: 91).
 int close_lanes(const Resolved& r, long long faces) {
     constexpr long long ROOM = 256 * 2 * WG;
     const int nodes = (r.D >= 1 ? r.nv[0] : 0) + (r.D >= 2 ? r.nv[1] : 0) + (r.D >= 3 ? r.nv[2] : 0);
-    if (16 * faces > ROOM && nodes <= 256) return 1;
+    const int rounds = nodes <= 256 ? 1 : (r.D == 1 ? 3 : 2);
+    if (16 * faces > rounds * ROOM) return 1;
     int l = 16;
     while (l < WG && nodes > 2 * l && 4 * l * faces <= ROOM) l *= 4;
     return l;

@@ -1,0 +1,58 @@
+"""Launch rules of the library's host side, asked of the built library without
+a GPU: a small program includes the library's internal header, links the
+library and prints what a rule answers."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+from paper_2208_09132_amd import cdugks as cd
+from tests.conftest import ROOT
+
+CSRC = os.path.join(ROOT, "paper_2208_09132_amd", "csrc")
+INCLUDES = ["-D__HIP_PLATFORM_AMD__", "-isystem", "/opt/rocm/include", "-I", os.path.join(ROOT, "include"), "-I", CSRC]
+
+
+def build(tmp, source, extra):
+    """Compile a host program with g++ and return its path."""
+    if shutil.which("g++") is None:
+        pytest.skip("no g++")
+    src, exe = os.path.join(tmp, "rules.cpp"), os.path.join(tmp, "rules")
+    with open(src, "w") as f:
+        f.write(source)
+    subprocess.run(["g++", "-std=c++17", "-O1", *INCLUDES, src, "-o", exe, *extra], check=True)
+    return exe
+
+
+@pytest.fixture(scope="module")
+def lanes(tmp_path_factory):
+    exe = build(str(tmp_path_factory.mktemp("rules")), r"""
+#include "cdugks_host.h"
+#include <cstdio>
+#include <cstdlib>
+int main(int argc, char** argv) {
+    cdg::Resolved r{};
+    r.D = atoi(argv[1]);
+    for (int d = 0; d < 3; ++d) r.nv[d] = d < r.D ? atoi(argv[2 + d]) : 1;
+    for (int k = 2 + r.D; k < argc; ++k) printf("%d ", cdg::close_lanes(r, atoll(argv[k])));
+}
+""", [cd.LIB_PATH, "-Wl,-rpath," + os.path.dirname(cd.LIB_PATH)])
+
+    def ask(nv, *faces):
+        args = [str(len(nv))] + [str(x) for x in (*nv, *faces)]
+        out = subprocess.run([exe, *args], check=True, stdout=subprocess.PIPE, text=True).stdout
+        return [int(x) for x in out.split()]
+
+    return ask
+
+
+def test_one_thread_closes_a_face_where_groups_would_queue(lanes):
+    # two workgroups of 256 on each of 256 CUs: 8192 groups of 16
+    assert lanes([28, 28], 8192, 8193, 131072) == [16, 1, 1]
+    # more than 256 nodes: groups of 16 for up to three (1-D) or two (2-D, 3-D)
+    # rounds of that, never for any number of faces
+    assert lanes([257], 8192, 24576, 24577, 200000, 16000000) == [16, 16, 1, 1, 1]
+    assert lanes([129, 129], 16384, 16385, 80000) == [16, 1, 1]
+    assert lanes([100, 100, 100], 16384, 16385) == [16, 1]
+    assert lanes([16385], 128, 24577) == [256, 1]
