@@ -21,7 +21,12 @@ __global__ __launch_bounds__(WG, (batched_face_waves<ST, MAXD>())) void k_face_s
     // problems, as fewer cells of the small ones are padding.)
     using K1 = FaceSumKernel<1, ST, DIR, SS, 0, ACC>;
     using K2 = FaceSumKernel<MAXD >= 2 ? 2 : 1, ST, DIR, SS, 0, ACC>;
-    using K3 = FaceSumKernel<MAXD >= 3 ? 3 : 1, ST, DIR, SS>;
+    // 3-D FP64 boxes stream their face values whatever the rows: measured (the
+    // reason is not known), four problems of 33^3 x 8^3 take 8.66 ms streamed,
+    // 9.05 with ordinary stores and 9.20 with the test per store of single
+    // problems; of 64 x 32 x 32 cells, whole sectors, 9.41, 9.44 and 9.79.
+    using K3 = FaceSumKernel<MAXD >= 3 ? 3 : 1, ST, DIR, SS, 0, false, true,
+                             std::is_same<ST, double>::value ? FV_STREAM : FV_EITHER>;
     __shared__ union U {
         typename K1::Smem s1;
         typename K2::Smem s2;

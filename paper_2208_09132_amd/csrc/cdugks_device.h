@@ -1434,8 +1434,11 @@ struct UpdateKernel {
                 load(i, off_of(i), ST{}, rg, rb, fv);
                 // every load before any of the arithmetic (3-D FP64; left to
                 // itself the compiler sinks some, 690 -> 661 us on 37 x 29 x 23
-                // cells x 11 x 10 x 12; FP32 gains nothing)
-                if constexpr (std::is_same<ST, double>::value) __builtin_amdgcn_sched_barrier(1);
+                // cells x 11 x 10 x 12; FP32 gains nothing).  Not in batches
+                // without an acceleration, whose two waves per SIMD it costs
+                // spills (four of 32^3 x 8^3: 1441 us with it, 1370 without;
+                // with an acceleration, one wave, 6.2 and 8.3 ms per step)
+                if constexpr (std::is_same<ST, double>::value && (CLOSE || ACC)) __builtin_amdgcn_sched_barrier(1);
                 velocity(i, off_of(i), ST{}, rg, rb, fv);
             }
         } else if constexpr (!StoreT<ST>::MIXED) {

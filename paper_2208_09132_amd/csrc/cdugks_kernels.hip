@@ -200,10 +200,19 @@ __global__ __launch_bounds__(WG, 2) void k_update(Problem P) {
     UpdateKernel<D, ST, ACC, ROWS>::run(P, (long long)blk * WG + threadIdx.x, slice, P.nslices_upd);
 }
 
+// Waves per SIMD the batched update is compiled for.  3-D FP64 takes 2: left to
+// itself it ends 4 registers above what two waves may have (four problems of
+// 32^3 x 8^3: 1942 us with one wave, 1370 with two).  With an acceleration one
+// wave wins (steps of the same problems 6.2 and 6.9 ms).
+template <typename ST, int MAXD, bool ACC>
+constexpr int batched_update_waves() { return MAXD == 3 && std::is_same<ST, double>::value && !ACC ? 2 : 1; }
+
 // ACC: the class's problems have an external acceleration
 template <typename ST, int MAXD, bool ACC>
-__global__ __launch_bounds__(WG) void k_update_batched(const Problem* probs, const WorkItem* items, int nitems,
-                                                       int* queue, int* other) {
+__global__ __launch_bounds__(WG, (batched_update_waves<ST, MAXD, ACC>())) void k_update_batched(const Problem* probs,
+                                                                                                const WorkItem* items,
+                                                                                                int nitems, int* queue,
+                                                                                                int* other) {
     __shared__ int slot;
     if (blockIdx.x == 0 && threadIdx.x == 0) *other = 0;
     for (int w = next_item(queue, &slot); w < nitems; w = next_item(queue, &slot)) {
