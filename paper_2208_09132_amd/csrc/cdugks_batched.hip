@@ -12,7 +12,8 @@ constexpr int batched_face_waves() { return MAXD <= 2 && !std::is_same<ST, doubl
 // ACC: the class's problems have an external acceleration (stage 1 of the
 // 1-D and 2-D face sums adds its source; 3-D problems load quarter-step
 // fields that already carry it)
-template <typename ST, int MAXD, bool DIR, bool SS, bool ACC>
+// SM2: how 2-D problems store their face values
+template <typename ST, int MAXD, bool DIR, bool SS, bool ACC, int SM2 = fv_store_mode<2>()>
 __global__ __launch_bounds__(WG, (batched_face_waves<ST, MAXD>())) void k_face_sums_batched(const Problem* probs, const WorkItem* items, int nitems,
                                                           int* queue, int* other) {
     // Tile shape 0 for every problem.  (32 x 8 tiles were faster in FP32 while
@@ -20,7 +21,7 @@ __global__ __launch_bounds__(WG, (batched_face_waves<ST, MAXD>())) void k_face_s
     // st_faces, 16 x 16 takes 2.05 against 2.11 ms per step of 20 uneven
     // problems, as fewer cells of the small ones are padding.)
     using K1 = FaceSumKernel<1, ST, DIR, SS, 0, ACC>;
-    using K2 = FaceSumKernel<MAXD >= 2 ? 2 : 1, ST, DIR, SS, 0, ACC>;
+    using K2 = FaceSumKernel<MAXD >= 2 ? 2 : 1, ST, DIR, SS, 0, ACC, true, MAXD >= 2 ? SM2 : fv_store_mode<1>()>;
     // 3-D FP64 boxes stream their face values whatever the rows: measured (the
     // reason is not known), four problems of 33^3 x 8^3 take 8.66 ms streamed,
     // 9.05 with ordinary stores and 9.20 with the test per store of single
@@ -60,9 +61,29 @@ __global__ __launch_bounds__(WG, (batched_face_waves<ST, MAXD>())) void k_face_s
         }                                                            \
     } while (0)
 
+// stream: every 2-D problem of the class has face rows of whole 64-byte
+// sectors.  2-D FP64 then streams the face values, as a single problem does
+// (see st_faces; steps streamed and not: two of 256^2 x 28^2 3245 and 3270 us,
+// forty of 64^2 x 20^2 2666 and 2722), which ragged rows would lose by (sixty
+// uneven problems 14.81 ms and 14.20).  With a test per store instead of a
+// kernel of its own: 3281 and 2692 us, 14.29 ms.
+template <typename ST, int MAXD, bool DIR, bool SS, bool ACC>
+static void launch_class(const Problem* probs, const WorkItem* items, int nitems, int grid, bool stream, int* queue,
+                         int* other, hipStream_t s) {
+    if constexpr (MAXD == 2 && std::is_same<ST, double>::value) {
+        if (stream) {
+            hipLaunchKernelGGL((k_face_sums_batched<ST, MAXD, DIR, SS, ACC, FV_STREAM>), dim3(grid), dim3(WG), 0, s,
+                               probs, items, nitems, queue, other);
+            return;
+        }
+    }
+    hipLaunchKernelGGL((k_face_sums_batched<ST, MAXD, DIR, SS, ACC>), dim3(grid), dim3(WG), 0, s, probs, items, nitems,
+                       queue, other);
+}
+
 hipError_t launch_face_sums_batched(const Problem* probs, const WorkItem* items, int nitems, int grid,
                                     int maxd, int storage, bool dirichlet, bool single_slope, bool accel,
-                                    int* queue, int* other, hipStream_t s) {
+                                    bool stream, int* queue, int* other, hipStream_t s) {
     if (nitems <= 0) return hipSuccess;
 #define CDG_B(DIRV, SSV, ACCV)                                                                               \
     do {                                                                                                     \
@@ -81,8 +102,7 @@ hipError_t launch_face_sums_batched(const Problem* probs, const WorkItem* items,
         }                                                                                                    \
     } while (0)
 #define CDG_LB(TT, MD, DIRV, SSV, ACCV)                                                                      \
-    hipLaunchKernelGGL((k_face_sums_batched<TT, MD, DIRV, SSV, ACCV>), dim3(grid), dim3(WG), 0, s, probs,   \
-                       items, nitems, queue, other)
+    launch_class<TT, MD, DIRV, SSV, ACCV>(probs, items, nitems, grid, stream, queue, other, s)
 #define STORAGE_ storage
     // the acceleration never comes with the single-slope option (refused at
     // problem set-up)

@@ -139,7 +139,7 @@ hipError_t launch_to_f64(const Problem& P, const void* src, int row0, int nrows,
 // per-problem prefix offsets (in threads).
 hipError_t launch_face_sums_batched(const Problem* probs, const WorkItem* items, int nitems, int grid,
                                     int maxd, int storage, bool dirichlet, bool single_slope, bool accel,
-                                    int* queue, int* other, hipStream_t s);
+                                    bool stream, int* queue, int* other, hipStream_t s);
 hipError_t launch_update_batched(const Problem* probs, const WorkItem* items, int nitems, int grid, int maxd,
                                  int storage, bool accel, int* queue, int* other, hipStream_t s);
 int batched_blocks_per_cu(int maxd, int storage, bool accel, bool update);

@@ -40,6 +40,7 @@ struct StorageClass {
     bool dirichlet = false;  // members have Dirichlet sides (face-sum variant)
     bool single_slope = false;  // members use the single-slope reconstruction
     bool accel = false;  // members have an external acceleration (kernel variants)
+    bool stream = false;  // every 2-D member's face rows are whole sectors (Problem::fv_stream)
     int maxd = 1;
     WorkItem* items_fs = nullptr;  // device
     int n_fs = 0, grid_fs = 0;
@@ -156,7 +157,8 @@ hipError_t enqueue_batch_step(cdugks_batch* b, int phase) {
     const Problem* probs = b->d_probs[phase];
     for (auto& c : b->classes)
         if ((e = launch_face_sums_batched(probs, c.items_fs, c.n_fs, c.grid_fs, c.maxd, c.storage, c.dirichlet,
-                                          c.single_slope, c.accel, c.queue, c.queue + 1, b->stream)) != hipSuccess)
+                                          c.single_slope, c.accel, c.stream, c.queue, c.queue + 1,
+                                          b->stream)) != hipSuccess)
             return e;
     if ((e = launch_face_close_batched(probs, b->d_face_off, np, b->maxd, b->close_groups, b->face_total,
                                        b->stream)) != hipSuccess)
@@ -294,6 +296,7 @@ int batch_build(cdugks_ctx* const* ctxs, int count, int chunk_steps, cdugks_batc
     std::vector<std::vector<WorkItem>> fs(NCLASS), up(NCLASS);
     std::vector<std::vector<double>> cfs(NCLASS), cup(NCLASS);
     int maxd[NCLASS] = {};
+    bool ragged[NCLASS] = {};          // some 2-D member's face rows cut sectors
     long long block_vel[NCLASS] = {};  // update blocks x velocities of the class
     auto class_of = [](const Resolved& r) {
         return ((2 * r.storage + (r.any_dirichlet ? 1 : 0)) * 2 + r.recon) * 2 + (r.has_accel ? 1 : 0);
@@ -302,6 +305,7 @@ int batch_build(cdugks_ctx* const* ctxs, int count, int chunk_steps, cdugks_batc
         const Resolved& r = ctxs[j]->r;
         const int s = class_of(r);
         maxd[s] = std::max(maxd[s], r.D);
+        if (r.D == 2 && !ctxs[j]->P.fv_stream) ragged[s] = true;
         block_vel[s] += (r.N + WG - 1) / WG * r.V;
     }
     const int cus = device_cus();
@@ -391,6 +395,7 @@ int batch_build(cdugks_ctx* const* ctxs, int count, int chunk_steps, cdugks_batc
         sc.single_slope = (s / 2) % 2 == 1;
         sc.accel = s % 2 == 1;
         sc.maxd = maxd[s];
+        sc.stream = !ragged[s];
         // persistent grids: resident slots (times the tuned factor of the
         // largest class member), never more than the work items
         int gf = 1;

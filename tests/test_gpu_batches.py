@@ -1,7 +1,8 @@
 """Batches against the same problems alone, bit for bit, in the forms whose
 kernels are compiled differently for batches: 3-D FP64 with and without an
-acceleration (register limits, face-value stores), on face grids whose rows
-fill whole 64-byte sectors and on ragged ones, and one of each together."""
+acceleration (register limits, face-value stores) and 2-D FP64 (face-value
+stores), on face grids whose rows fill whole 64-byte sectors and on ragged
+ones, and one of each together."""
 import numpy as np
 import pytest
 
@@ -48,3 +49,13 @@ SECTORS, RAGGED = [16, 8, 8], [17, 6, 9]
 def test_3d_fp64(sizes, accel):
     kw = {} if accel is None else dict(accel=accel)
     check([fourier(n, [7, 6, 5], "f64", 3 + k, **kw) for k, n in enumerate(sizes)])
+
+
+@pytest.mark.parametrize("form", ["plain", "accel", "single_slope", "dirichlet"])
+@pytest.mark.parametrize("n0", [[24, 40], [23, 33], [24, 23]])
+def test_2d_fp64(n0, form):
+    kw = {"plain": {}, "accel": dict(accel=[0.1, -0.05]), "single_slope": dict(reconstruction="single_slope"),
+          "dirichlet": dict(bc=["periodic", "dirichlet"], dirichlet=[None, [[1.0, 0.0, 0.0, 1.0]] * 2])}[form]
+    # with a 1-D problem beside them, whose rows do not count
+    check([fourier([m, 19], [8, 7], "f64", m, **kw) for m in n0] +
+          ([wl.sod(n=50, nv=12)] if form == "plain" else []))
