@@ -788,6 +788,7 @@ int cdugks_autotune(cdugks_ctx* c, int steps_per_trial) {
             P.tile = t;
             for (int d = 0; d < 3; ++d) P.tiles1[d] = rt.tiles1[d];
             for (int d = 0; d < 2; ++d) P.column[d] = rt.column[d];
+            P.value_slices = value_slices(rt);
             float ms = 0.f;
             hipError_t he = launch_face_sums(P, c->stream);  // warm-up
             if (he == hipSuccess) he = hipEventRecord(e0, c->stream);
@@ -854,6 +855,7 @@ int cdugks_autotune(cdugks_ctx* c, int steps_per_trial) {
     c->P.tile = c->r.tile;
     for (int d = 0; d < 3; ++d) c->P.tiles1[d] = c->r.tiles1[d];
     for (int d = 0; d < 2; ++d) c->P.column[d] = c->r.column[d];
+    c->P.value_slices = value_slices(c->r);
     for (int k = 0; k < 2; ++k)
         if (c->graph[k]) {
             (void)hipGraphExecDestroy(c->graph[k]);
