@@ -272,9 +272,10 @@ int cdugks_info(cdugks_ctx* ctx, double* dt, double* t, int64_t* steps);
 
 /* Timing helper: advance nsteps steps launching every phase on its own, with
  * HIP events recorded between the phases on the context's stream; ms[4]
- * receives the mean duration per step (milliseconds) of a step's phases: face
- * sums, face closure, 0 (the cell closure is part of the update), update.
- * Waits for the stream. */
+ * receives the mean duration per step (milliseconds) of the four phases of a
+ * step: face sums, face closure, cell closure, update.  Outside this helper a
+ * step has no launch for the cell closure, which its update forms in passing:
+ * it takes about the sum of the other three.  Waits for the stream. */
 int cdugks_profile_phases(cdugks_ctx* ctx, int64_t nsteps, double* ms);
 
 /* Release the context (waits for its stream).  NULL-safe.  A context that

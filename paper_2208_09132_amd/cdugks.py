@@ -350,8 +350,9 @@ class Solver:
 
     def profile_phases(self, nsteps: int):
         """Mean per-step kernel durations (ms) from HIP events on the context's
-        stream: face sums, face closure, zero (the cell closure is part of
-        the update), update."""
+        stream: face sums, face closure, cell closure, update.  A step has no
+        launch for the cell closure, which its update forms in passing: it
+        takes about the sum of the other three."""
         ms = np.zeros(4)
         check(load_library().cdugks_profile_phases(self.ctx, int(nsteps), _ptr(ms)))
         return ms

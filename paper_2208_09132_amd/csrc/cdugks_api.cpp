@@ -1080,8 +1080,8 @@ int cdugks_info(cdugks_ctx* c, double* dt, double* t, int64_t* steps) {
 int cdugks_profile_phases(cdugks_ctx* c, int64_t nsteps, double* ms) {
     if (!c || !ms || nsteps <= 0) return fail(CDUGKS_ERR_INVALID, "bad argument");
     if (c->sticky) return fail(c->sticky, "context is in an error state");
-    hipEvent_t ev[4];
-    for (int k = 0; k < 4; ++k)
+    hipEvent_t ev[5];
+    for (int k = 0; k < 5; ++k)
         if (hipEventCreate(&ev[k]) != hipSuccess) return fail(CDUGKS_ERR_DEVICE, "event create");
     double acc[4] = {0, 0, 0, 0};
     hipError_t e = hipSuccess;
@@ -1093,19 +1093,21 @@ int cdugks_profile_phases(cdugks_ctx* c, int64_t nsteps, double* ms) {
         if (e == hipSuccess) e = hipEventRecord(ev[1], c->stream);
         if (e == hipSuccess) e = launch_face_close(P, c->stream);
         if (e == hipSuccess) e = hipEventRecord(ev[2], c->stream);
-        if (e == hipSuccess) e = launch_update(P, c->stream);
+        // the update writes the same values again
+        if (e == hipSuccess) e = launch_cell_close(P, c->stream);
         if (e == hipSuccess) e = hipEventRecord(ev[3], c->stream);
-        if (e == hipSuccess) e = hipEventSynchronize(ev[3]);
-        // ms[2], the cell closure, is part of the update's launch: zero
-        for (int k = 0; k < 3 && e == hipSuccess; ++k) {
+        if (e == hipSuccess) e = launch_update(P, c->stream);
+        if (e == hipSuccess) e = hipEventRecord(ev[4], c->stream);
+        if (e == hipSuccess) e = hipEventSynchronize(ev[4]);
+        for (int k = 0; k < 4 && e == hipSuccess; ++k) {
             float t = 0.f;
             e = hipEventElapsedTime(&t, ev[k], ev[k + 1]);
-            acc[k == 2 ? 3 : k] += t;
+            acc[k] += t;
         }
         c->cur = 1 - c->cur;
         c->steps += 1;
     }
-    for (int k = 0; k < 4; ++k) (void)hipEventDestroy(ev[k]);
+    for (int k = 0; k < 5; ++k) (void)hipEventDestroy(ev[k]);
     if (e != hipSuccess) return hip_fail(e, "profiled step");
     for (int k = 0; k < 4; ++k) ms[k] = acc[k] / (double)nsteps;
     return cdugks_sync(c);

@@ -123,6 +123,7 @@ int batched_face_blocks_per_cu(int maxd, int storage, bool accel);
 // on its own velocity grid; same cells and storage form.
 hipError_t launch_regrid(const Problem& Pn, const Problem& Po, hipStream_t s);
 hipError_t launch_face_close(const Problem& P, hipStream_t s);
+hipError_t launch_cell_close(const Problem& P, hipStream_t s);
 hipError_t launch_update(const Problem& P, hipStream_t s);
 hipError_t launch_moments(const Problem& P, const double* W, double* rho, double* u, double* T,
                           hipStream_t s);

@@ -260,6 +260,13 @@ __device__ __forceinline__ void cell_close_one(const Problem& P, long long c) {
     cell_close<D>(P, c, fl, fr, true);
 }
 
+// A problem's cell closure on its own (cdugks_profile_phases; a step's update
+// closes its cells itself)
+template <int D>
+__global__ __launch_bounds__(WG) void k_cell_close(Problem P) {
+    cell_close_one<D>(P, (long long)blockIdx.x * WG + threadIdx.x);
+}
+
 __global__ __launch_bounds__(WG) void k_cell_close_batched(const Problem* probs, const long long* offsets,
                                                            int nprob, long long total) {
     const long long g0 = (long long)blockIdx.x * WG;
@@ -427,6 +434,14 @@ hipError_t launch_face_close(const Problem& P, hipStream_t s) {
     else if (P.D == 2) CDG_L(2);
     else CDG_L(3);
 #undef CDG_L
+    return hipGetLastError();
+}
+
+hipError_t launch_cell_close(const Problem& P, hipStream_t s) {
+    const dim3 grid(blocks_for(P.N));
+    if (P.D == 1) hipLaunchKernelGGL(k_cell_close<1>, grid, dim3(WG), 0, s, P);
+    else if (P.D == 2) hipLaunchKernelGGL(k_cell_close<2>, grid, dim3(WG), 0, s, P);
+    else hipLaunchKernelGGL(k_cell_close<3>, grid, dim3(WG), 0, s, P);
     return hipGetLastError();
 }
 
