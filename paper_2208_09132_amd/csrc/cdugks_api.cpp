@@ -697,9 +697,32 @@ static int scratch_on_device(int dev, double** out) {
     return CDUGKS_OK;
 }
 
-int init_context(const cdugks_space* space, const cdugks_velocity* vel, const cdugks_params* params,
-                 const double* rho, const double* u, const double* T, void* hip_stream, void* arena,
-                 size_t arena_bytes, size_t most, cdugks_ctx** out) {
+}  // namespace cdg
+
+using namespace cdg;
+
+// ---------------------------------------------------------------------------
+// C ABI
+// ---------------------------------------------------------------------------
+extern "C" {
+
+const char* cdugks_last_error(void) { return g_last_error.c_str(); }
+
+int cdugks_required_bytes(const cdugks_space* space, const cdugks_velocity* vel,
+                          const cdugks_params* params, size_t* bytes) {
+    if (!bytes) return fail(CDUGKS_ERR_INVALID, "null bytes pointer");
+    cdugks_params p = *params;
+    if (p.relax_mode == CDUGKS_RELAX_KN && !(p.rho_ref > 0.0)) p.rho_ref = 1.0;  // size does not depend on it
+    Resolved r;
+    int rc = resolve(space, vel, &p, nullptr, &r);
+    if (rc) return rc;
+    *bytes = r.bytes;
+    return CDUGKS_OK;
+}
+
+int cdugks_init(const cdugks_space* space, const cdugks_velocity* vel, const cdugks_params* params,
+                const double* rho, const double* u, const double* T, void* hip_stream, void* arena,
+                size_t arena_bytes, cdugks_ctx** out) {
     if (!out) return fail(CDUGKS_ERR_INVALID, "null output pointer");
     *out = nullptr;
     if (!rho || !u || !T) return fail(CDUGKS_ERR_INVALID, "null moment array");
@@ -753,7 +776,7 @@ int init_context(const cdugks_space* space, const cdugks_velocity* vel, const cd
         c->own_memory = false;
     } else {
         void* p = nullptr;
-        e = pool_take(c->device, r.bytes, most, &p, &c->own_bytes);
+        e = pool_take(c->device, r.bytes, &p);
         if (e != hipSuccess) {
             if (c->own_stream) (void)hipStreamDestroy(c->stream);
             delete c;
@@ -819,35 +842,6 @@ int init_context(const cdugks_space* space, const cdugks_velocity* vel, const cd
     }
     *out = c;
     return CDUGKS_OK;
-}
-
-}  // namespace cdg
-
-using namespace cdg;
-
-// ---------------------------------------------------------------------------
-// C ABI
-// ---------------------------------------------------------------------------
-extern "C" {
-
-const char* cdugks_last_error(void) { return g_last_error.c_str(); }
-
-int cdugks_required_bytes(const cdugks_space* space, const cdugks_velocity* vel,
-                          const cdugks_params* params, size_t* bytes) {
-    if (!bytes) return fail(CDUGKS_ERR_INVALID, "null bytes pointer");
-    cdugks_params p = *params;
-    if (p.relax_mode == CDUGKS_RELAX_KN && !(p.rho_ref > 0.0)) p.rho_ref = 1.0;  // size does not depend on it
-    Resolved r;
-    int rc = resolve(space, vel, &p, nullptr, &r);
-    if (rc) return rc;
-    *bytes = r.bytes;
-    return CDUGKS_OK;
-}
-
-int cdugks_init(const cdugks_space* space, const cdugks_velocity* vel, const cdugks_params* params,
-                const double* rho, const double* u, const double* T, void* hip_stream, void* arena,
-                size_t arena_bytes, cdugks_ctx** out) {
-    return init_context(space, vel, params, rho, u, T, hip_stream, arena, arena_bytes, SIZE_MAX, out);
 }
 
 int cdugks_regrid(cdugks_ctx* src, const cdugks_space* space, const cdugks_velocity* vel,
@@ -1007,10 +1001,9 @@ int cdugks_distributions(cdugks_ctx* c, double* g, double* b) {
     const Resolved& r = c->r;
     size_t n = (size_t)r.N * r.V;
     void* block = nullptr;
-    size_t block_bytes = 0;
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
-    if (e == hipSuccess) e = pool_take(dev, n * 8, SIZE_MAX, &block, &block_bytes);
+    if (e == hipSuccess) e = pool_take(dev, n * 8, &block);
     if (e != hipSuccess) return hip_fail(e, "temporary allocation");
     double* const tmp = (double*)block;
     double* outs[2] = {g, b};
@@ -1022,7 +1015,7 @@ int cdugks_distributions(cdugks_ctx* c, double* g, double* b) {
     }
     // after a failed copy work may still be in flight on the block
     if (e != hipSuccess) (void)hipFree(block);
-    else pool_give(dev, block, block_bytes);
+    else pool_give(dev, block, n * 8);
     return e == hipSuccess ? CDUGKS_OK : hip_fail(e, "distribution copy");
 }
 
@@ -1125,7 +1118,7 @@ void cdugks_destroy(cdugks_ctx* c) {
     for (int k = 0; k < 2; ++k)
         if (c->graph[k]) (void)hipGraphExecDestroy(c->graph[k]);
     if (c->own_memory && c->base) {
-        if (idle) pool_give(c->device, c->base, c->own_bytes);
+        if (idle) pool_give(c->device, c->base, c->r.bytes);
         else (void)hipFree(c->base);
     }
     if (c->counted) pool_user(c->device, -1);

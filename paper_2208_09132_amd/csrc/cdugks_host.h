@@ -53,19 +53,15 @@ void velocity_tables(const Resolved& r, std::vector<double>& vel, std::vector<do
 void dirichlet_tables(const Resolved& r, const std::vector<double>& vel, std::vector<double>& out);
 int value_slices(const Resolved& r);
 int close_lanes(const Resolved& r, long long faces);
-// Device memory (cdugks_pool.cpp): a block of at least `bytes` and at most
-// `most` bytes, its size in *got, from the idle blocks of the current device
-// or newly allocated; pool_give returns one on which no work is in flight.
-// pool_user counts the live contexts and servers idle blocks are kept for;
-// pool_trim gives idle blocks back until at most `keep` bytes are held.
-hipError_t pool_take(int device, size_t bytes, size_t most, void** ptr, size_t* got);
+// Device memory (cdugks_pool.cpp): a block of `bytes` bytes, an idle one of the
+// current device or newly allocated; pool_give returns one on which no work is
+// in flight.  pool_user counts the live contexts and servers idle blocks are
+// kept for; pool_trim gives idle blocks back until at most `keep` bytes are
+// held.
+hipError_t pool_take(int device, size_t bytes, void** ptr);
 void pool_give(int device, void* ptr, size_t bytes);
 void pool_trim(int device, size_t keep);
 void pool_user(int device, int change);
-// cdugks_init whose own allocation takes at most `most` bytes
-int init_context(const cdugks_space* space, const cdugks_velocity* vel, const cdugks_params* params,
-                 const double* rho, const double* u, const double* T, void* hip_stream, void* arena,
-                 size_t arena_bytes, size_t most, cdugks_ctx** out);
 void fill_problem(const Resolved& r, char* base, Problem& P);
 long long tail_rows(const Resolved& r, const std::vector<double>& vel, const double* u, const double* T,
                     std::vector<long long>& rows);
@@ -90,7 +86,6 @@ struct cdugks_ctx {
     int device = 0;           // the device current at cdugks_init
     char* base = nullptr;
     bool own_memory = false;
-    size_t own_bytes = 0;  // size of the own block (at least r.bytes)
     bool counted = false;  // counted as a user of the device's idle blocks
     int cur = 0;          // buffer parity holding the current state
     int64_t steps = 0;

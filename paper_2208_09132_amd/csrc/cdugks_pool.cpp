@@ -9,8 +9,9 @@
 // Per device, idle blocks are kept while the library has a live context or
 // server there, up to 1/32 of the device's memory in all, the oldest going
 // first; with the last of them (and whenever an allocation fails) everything
-// idle is given back.  A block is reused for a request of at least 4/5 of its
-// size.  An object releases its block only after waiting for the streams that
+// idle is given back.  A block is reused for a request of exactly its size, so
+// an object never holds more than it asked for: what fitted the device or a
+// server's budget without kept blocks fits with them.  An object releases its block only after waiting for the streams that
 // used it, so a block taken here has no work in flight.
 #include "cdugks_host.h"
 
@@ -80,23 +81,16 @@ bool cut(int device, size_t keep, int most = MAX_IDLE) {
 
 }  // namespace
 
-hipError_t pool_take(int device, size_t bytes, size_t most, void** ptr, size_t* got) {
+hipError_t pool_take(int device, size_t bytes, void** ptr) {
     {
         std::lock_guard<std::mutex> lock(g_pools.mu);
         DevicePool* p = pool_of(device);
-        int best = -1;
-        for (int k = 0; p && k < p->count; ++k) {
-            const size_t b = p->idle[k].bytes;
-            if (b >= bytes && b <= most && b - bytes <= b / 5 && (best < 0 || b < p->idle[best].bytes)) best = k;
-        }
-        if (best >= 0) {
-            const Block b = remove(*p, best);
-            *ptr = b.ptr;
-            *got = b.bytes;
-            return hipSuccess;
-        }
+        for (int k = 0; p && k < p->count; ++k)
+            if (p->idle[k].bytes == bytes) {
+                *ptr = remove(*p, k).ptr;
+                return hipSuccess;
+            }
     }
-    *got = bytes;
     hipError_t e = hipMalloc(ptr, bytes);
     if (e != hipSuccess && cut(device, 0)) {
         (void)hipGetLastError();

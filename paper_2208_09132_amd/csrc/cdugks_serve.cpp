@@ -362,8 +362,9 @@ int batch_build(cdugks_ctx* const* ctxs, int count, int chunk_steps, cdugks_batc
     }
     void* block = nullptr;
     hipError_t e = hipGetDevice(&b->device);
-    if (e == hipSuccess) e = pool_take(b->device, bytes, SIZE_MAX, &block, &b->dev_bytes);
+    if (e == hipSuccess) e = pool_take(b->device, bytes, &block);
     b->dev = (char*)block;
+    b->dev_bytes = bytes;
     if (e != hipSuccess) {
         (void)hipGetLastError();
         delete b;
@@ -527,16 +528,15 @@ void server_loop(cdugks_server* s) {
         }
         for (Request* r : admit) {
             r->t_admit = now_s();
-            // idle blocks count against the budget, and a reused block may be
-            // larger than the request only by what the budget still allows
+            // idle blocks count against the budget
             size_t room = 0;
             {
                 std::lock_guard<std::mutex> lock(s->mu);
                 room = s->budget - s->used;
             }
             pool_trim(s->device, room);
-            int rc = init_context(&r->sp, &r->ve, &r->pa, r->rho.data(), r->u.data(), r->T.data(), s->stream,
-                                  nullptr, 0, r->bytes + room, &r->ctx);
+            int rc = cdugks_init(&r->sp, &r->ve, &r->pa, r->rho.data(), r->u.data(), r->T.data(), s->stream,
+                                 nullptr, 0, &r->ctx);
             std::lock_guard<std::mutex> lock(s->mu);
             if (rc) {
                 r->status = rc;
@@ -546,8 +546,6 @@ void server_loop(cdugks_server* s) {
                 s->cv.notify_all();
                 continue;
             }
-            s->used += r->ctx->own_bytes - r->bytes;
-            r->bytes = r->ctx->own_bytes;
             r->remaining = r->nsteps;
             s->active.push_back(r);
             dirty = true;
