@@ -697,32 +697,9 @@ static int scratch_on_device(int dev, double** out) {
     return CDUGKS_OK;
 }
 
-}  // namespace cdg
-
-using namespace cdg;
-
-// ---------------------------------------------------------------------------
-// C ABI
-// ---------------------------------------------------------------------------
-extern "C" {
-
-const char* cdugks_last_error(void) { return g_last_error.c_str(); }
-
-int cdugks_required_bytes(const cdugks_space* space, const cdugks_velocity* vel,
-                          const cdugks_params* params, size_t* bytes) {
-    if (!bytes) return fail(CDUGKS_ERR_INVALID, "null bytes pointer");
-    cdugks_params p = *params;
-    if (p.relax_mode == CDUGKS_RELAX_KN && !(p.rho_ref > 0.0)) p.rho_ref = 1.0;  // size does not depend on it
-    Resolved r;
-    int rc = resolve(space, vel, &p, nullptr, &r);
-    if (rc) return rc;
-    *bytes = r.bytes;
-    return CDUGKS_OK;
-}
-
-int cdugks_init(const cdugks_space* space, const cdugks_velocity* vel, const cdugks_params* params,
-                const double* rho, const double* u, const double* T, void* hip_stream, void* arena,
-                size_t arena_bytes, cdugks_ctx** out) {
+int init_context(const cdugks_space* space, const cdugks_velocity* vel, const cdugks_params* params,
+                 const double* rho, const double* u, const double* T, void* hip_stream, void* arena,
+                 size_t arena_bytes, size_t keep, cdugks_ctx** out) {
     if (!out) return fail(CDUGKS_ERR_INVALID, "null output pointer");
     *out = nullptr;
     if (!rho || !u || !T) return fail(CDUGKS_ERR_INVALID, "null moment array");
@@ -776,7 +753,7 @@ int cdugks_init(const cdugks_space* space, const cdugks_velocity* vel, const cdu
         c->own_memory = false;
     } else {
         void* p = nullptr;
-        e = pool_take(c->device, r.bytes, &p);
+        e = pool_take(c->device, r.bytes, keep, &p);
         if (e != hipSuccess) {
             if (c->own_stream) (void)hipStreamDestroy(c->stream);
             delete c;
@@ -842,6 +819,35 @@ int cdugks_init(const cdugks_space* space, const cdugks_velocity* vel, const cdu
     }
     *out = c;
     return CDUGKS_OK;
+}
+
+}  // namespace cdg
+
+using namespace cdg;
+
+// ---------------------------------------------------------------------------
+// C ABI
+// ---------------------------------------------------------------------------
+extern "C" {
+
+const char* cdugks_last_error(void) { return g_last_error.c_str(); }
+
+int cdugks_required_bytes(const cdugks_space* space, const cdugks_velocity* vel,
+                          const cdugks_params* params, size_t* bytes) {
+    if (!bytes) return fail(CDUGKS_ERR_INVALID, "null bytes pointer");
+    cdugks_params p = *params;
+    if (p.relax_mode == CDUGKS_RELAX_KN && !(p.rho_ref > 0.0)) p.rho_ref = 1.0;  // size does not depend on it
+    Resolved r;
+    int rc = resolve(space, vel, &p, nullptr, &r);
+    if (rc) return rc;
+    *bytes = r.bytes;
+    return CDUGKS_OK;
+}
+
+int cdugks_init(const cdugks_space* space, const cdugks_velocity* vel, const cdugks_params* params,
+                const double* rho, const double* u, const double* T, void* hip_stream, void* arena,
+                size_t arena_bytes, cdugks_ctx** out) {
+    return init_context(space, vel, params, rho, u, T, hip_stream, arena, arena_bytes, SIZE_MAX, out);
 }
 
 int cdugks_regrid(cdugks_ctx* src, const cdugks_space* space, const cdugks_velocity* vel,
@@ -1003,7 +1009,7 @@ int cdugks_distributions(cdugks_ctx* c, double* g, double* b) {
     void* block = nullptr;
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
-    if (e == hipSuccess) e = pool_take(dev, n * 8, &block);
+    if (e == hipSuccess) e = pool_take(dev, n * 8, SIZE_MAX, &block);
     if (e != hipSuccess) return hip_fail(e, "temporary allocation");
     double* const tmp = (double*)block;
     double* outs[2] = {g, b};

@@ -54,14 +54,16 @@ void dirichlet_tables(const Resolved& r, const std::vector<double>& vel, std::ve
 int value_slices(const Resolved& r);
 int close_lanes(const Resolved& r, long long faces);
 // Device memory (cdugks_pool.cpp): a block of `bytes` bytes, an idle one of the
-// current device or newly allocated; pool_give returns one on which no work is
-// in flight.  pool_user counts the live contexts and servers idle blocks are
-// kept for; pool_trim gives idle blocks back until at most `keep` bytes are
-// held.
-hipError_t pool_take(int device, size_t bytes, void** ptr);
+// current device or newly allocated; of the other idle blocks at most `keep`
+// bytes stay.  pool_give returns one on which no work is in flight.  pool_user
+// counts the live contexts and servers idle blocks are kept for.
+hipError_t pool_take(int device, size_t bytes, size_t keep, void** ptr);
 void pool_give(int device, void* ptr, size_t bytes);
-void pool_trim(int device, size_t keep);
 void pool_user(int device, int change);
+// cdugks_init that leaves at most `keep` bytes of idle blocks
+int init_context(const cdugks_space* space, const cdugks_velocity* vel, const cdugks_params* params,
+                 const double* rho, const double* u, const double* T, void* hip_stream, void* arena,
+                 size_t arena_bytes, size_t keep, cdugks_ctx** out);
 void fill_problem(const Resolved& r, char* base, Problem& P);
 long long tail_rows(const Resolved& r, const std::vector<double>& vel, const double* u, const double* T,
                     std::vector<long long>& rows);

@@ -81,15 +81,18 @@ bool cut(int device, size_t keep, int most = MAX_IDLE) {
 
 }  // namespace
 
-hipError_t pool_take(int device, size_t bytes, void** ptr) {
+hipError_t pool_take(int device, size_t bytes, size_t keep, void** ptr) {
+    void* found = nullptr;
     {
         std::lock_guard<std::mutex> lock(g_pools.mu);
         DevicePool* p = pool_of(device);
-        for (int k = 0; p && k < p->count; ++k)
-            if (p->idle[k].bytes == bytes) {
-                *ptr = remove(*p, k).ptr;
-                return hipSuccess;
-            }
+        for (int k = 0; p && !found && k < p->count; ++k)
+            if (p->idle[k].bytes == bytes) found = remove(*p, k).ptr;
+    }
+    cut(device, keep);
+    if (found) {
+        *ptr = found;
+        return hipSuccess;
     }
     hipError_t e = hipMalloc(ptr, bytes);
     if (e != hipSuccess && cut(device, 0)) {
@@ -120,8 +123,6 @@ void pool_give(int device, void* ptr, size_t bytes) {
     }
     (void)hipFree(ptr);
 }
-
-void pool_trim(int device, size_t keep) { cut(device, keep); }
 
 void pool_user(int device, int change) {
     bool last = false;

@@ -362,7 +362,7 @@ int batch_build(cdugks_ctx* const* ctxs, int count, int chunk_steps, cdugks_batc
     }
     void* block = nullptr;
     hipError_t e = hipGetDevice(&b->device);
-    if (e == hipSuccess) e = pool_take(b->device, bytes, &block);
+    if (e == hipSuccess) e = pool_take(b->device, bytes, SIZE_MAX, &block);
     b->dev = (char*)block;
     b->dev_bytes = bytes;
     if (e != hipSuccess) {
@@ -528,15 +528,15 @@ void server_loop(cdugks_server* s) {
         }
         for (Request* r : admit) {
             r->t_admit = now_s();
-            // idle blocks count against the budget
+            // idle blocks count against the budget, except the one the request
+            // itself takes
             size_t room = 0;
             {
                 std::lock_guard<std::mutex> lock(s->mu);
                 room = s->budget - s->used;
             }
-            pool_trim(s->device, room);
-            int rc = cdugks_init(&r->sp, &r->ve, &r->pa, r->rho.data(), r->u.data(), r->T.data(), s->stream,
-                                 nullptr, 0, &r->ctx);
+            int rc = init_context(&r->sp, &r->ve, &r->pa, r->rho.data(), r->u.data(), r->T.data(), s->stream,
+                                  nullptr, 0, room, &r->ctx);
             std::lock_guard<std::mutex> lock(s->mu);
             if (rc) {
                 r->status = rc;
