@@ -38,6 +38,9 @@ struct DevicePool {
 };
 struct Pools {
     std::mutex mu;
+    // held while idle blocks are freed, so that a thread that finds nothing
+    // left to free has waited for what others were freeing; taken before mu
+    std::mutex freeing;
     DevicePool dev[MAX_DEVICES];
 };
 // constant-initialised and without a destructor to run: usable whatever order
@@ -69,12 +72,13 @@ Block remove(DevicePool& p, int k) {
 bool cut(int device, size_t keep, int most = MAX_IDLE) {
     Block drop[MAX_IDLE];
     int n = 0;
+    std::lock_guard<std::mutex> free_lock(g_pools.freeing);
     {
         std::lock_guard<std::mutex> lock(g_pools.mu);
         DevicePool* p = pool_of(device);
         while (p && p->count > 0 && (p->held > keep || p->count > most)) drop[n++] = remove(*p, 0);
     }
-    // outside the lock: a free waits for the device
+    // outside mu: a free waits for the device
     for (int k = 0; k < n; ++k) (void)hipFree(drop[k].ptr);
     return n > 0;
 }
@@ -89,14 +93,17 @@ hipError_t pool_take(int device, size_t bytes, size_t keep, void** ptr) {
         for (int k = 0; p && !found && k < p->count; ++k)
             if (p->idle[k].bytes == bytes) found = remove(*p, k).ptr;
     }
-    cut(device, keep);
+    if (keep != SIZE_MAX) cut(device, keep);
     if (found) {
         *ptr = found;
         return hipSuccess;
     }
     hipError_t e = hipMalloc(ptr, bytes);
-    if (e != hipSuccess && cut(device, 0)) {
+    // idle blocks, of this thread's freeing or another's, may have been in the
+    // way; again while there were any
+    for (bool freed = true; e != hipSuccess && freed;) {
         (void)hipGetLastError();
+        freed = cut(device, 0);
         e = hipMalloc(ptr, bytes);
     }
     return e;

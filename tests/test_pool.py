@@ -136,6 +136,21 @@ static void budget() {
     CHECK(take(50, 10) != nullptr && frees == 2 && used == 90);
 }
 
+static void two_threads() {
+    void *a = take(100), *b = take(3060);
+    CHECK(b != nullptr);
+    pool_give(0, a, 100);
+    free_ms = 200;
+    // the first thread gives the idle block back for its 50 bytes; the second
+    // comes while the block is still on its way and there is nothing idle left
+    void* p[2] = {nullptr, nullptr};
+    std::thread first([&] { p[0] = take(50); });
+    while (freeing == 0) std::this_thread::sleep_for(std::chrono::milliseconds(1));
+    p[1] = take(50);
+    first.join();
+    CHECK(p[0] && p[1] && used == 3160);
+}
+
 int main(int, char** argv) {
     const std::string what = argv[1];
     if (what == "count") device = 3200000;  // bound 100000 bytes: the number of blocks is what counts
@@ -146,6 +161,7 @@ int main(int, char** argv) {
     else if (what == "last_user") last_user();
     else if (what == "out_of_memory") out_of_memory();
     else if (what == "budget") budget();
+    else if (what == "two_threads") two_threads();
     else return 2;
     return 0;
 }
@@ -157,7 +173,7 @@ def program(tmp_path_factory):
     return build(str(tmp_path_factory.mktemp("pool")), SOURCE, ["-pthread"])
 
 
-@pytest.mark.parametrize("what", ["exact", "bound", "count", "last_user", "out_of_memory", "budget"])
+@pytest.mark.parametrize("what", ["exact", "bound", "count", "last_user", "out_of_memory", "budget", "two_threads"])
 def test_pool(program, what):
     r = subprocess.run([program, what], stdout=subprocess.PIPE, text=True, timeout=60)
     assert r.returncode == 0, r.stdout
