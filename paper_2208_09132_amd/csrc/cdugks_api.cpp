@@ -547,6 +547,14 @@ int close_lanes(const Resolved& r, long long faces) {
     return l;
 }
 
+// Whether face values are stored with streaming stores where the kernel has
+// both kinds (st_faces, with the measurements): on face rows of whole 64-byte
+// sectors, in the 2-D FP32 forms of many velocities alone.
+bool fv_streams(const Resolved& r) {
+    const bool f64 = r.storage == CDUGKS_STORE_F64;
+    return (long long)r.ne[0] * (f64 ? 8 : 4) % 64 == 0 && (f64 || r.D != 2 || r.V >= 4096);
+}
+
 void fill_problem(const Resolved& r, char* base, Problem& P) {
     std::memset(&P, 0, sizeof P);
     P.D = r.D;
@@ -596,7 +604,7 @@ void fill_problem(const Resolved& r, char* base, Problem& P) {
     P.rows = r.storage == CDUGKS_STORE_F32_BF16TAIL ? (const long long*)(base + r.off_rows) : nullptr;
     P.recon = r.recon;
     P.tile = r.tile;
-    P.fv_stream = (long long)r.ne[0] * (r.storage == CDUGKS_STORE_F64 ? 8 : 4) % 64 == 0;
+    P.fv_stream = fv_streams(r);
     P.value_slices = value_slices(r);
     P.close_lanes = close_lanes(r, r.NE * r.D);
     P.has_accel = r.has_accel ? 1 : 0;

@@ -96,8 +96,9 @@ __device__ __forceinline__ E at_byte(const E* row, unsigned b) {
 // ordinary, face sums: 191^2 x 21^2 FP64 441 / 273 us, 310^2 x 18^2 FP32 551 /
 // 377 us, 41^3 x 10^3 FP32 2.81 / 1.38 ms.  On whole sectors streaming wins in
 // FP64, as the update then finds g and b in L2 (256^2 x 28^2, both phases: 1348
-// / 1385 us); in FP32, whose 16-wide tile rows are one sector, it does not (896
-// / 885 us).
+// / 1385 us); in FP32, whose 16-wide tile rows are one sector, only over 4096
+// velocities and more (256^2 cells x 28^2, 64^2, 80^2, 129^2: 896 / 885, 4830 /
+// 4860, 7430 / 7760, 19300 / 20160 us), which fv_streams leaves out below that.
 enum { FV_STREAM = 0, FV_ORDINARY = 1, FV_EITHER = 2 };
 // What a face-sum kernel takes unless told otherwise: 1-D tiles are rows of
 // whole lines; a test per store (EITHER) costs the 2-D kernels 2%, the 3-D ones
@@ -1595,7 +1596,7 @@ hipError_t launch_face_sums_shape(const Problem& P, hipStream_t s) {
                 return launch_face_reduce<D, typename StoreT<ST>::C>(P, s);
             }
         }
-        if constexpr (D == 2 && std::is_same<ST, double>::value) {
+        if constexpr (D == 2 && (TID == 0 || std::is_same<ST, double>::value)) {
             if (P.fv_stream) {
                 hipLaunchKernelGGL((k_face_sums<D, ST, DIR, SS, TID, ACC, true, FV_STREAM>), dim3(nt * P.nslices),
                                    dim3(tile_threads(D, TID)), 0, s, P);

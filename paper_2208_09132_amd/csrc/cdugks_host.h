@@ -53,6 +53,7 @@ void velocity_tables(const Resolved& r, std::vector<double>& vel, std::vector<do
 void dirichlet_tables(const Resolved& r, const std::vector<double>& vel, std::vector<double>& out);
 int value_slices(const Resolved& r);
 int close_lanes(const Resolved& r, long long faces);
+bool fv_streams(const Resolved& r);
 // Device memory (cdugks_pool.cpp): a block of `bytes` bytes, an idle one of the
 // current device or newly allocated; of the other idle blocks at most `keep`
 // bytes stay.  pool_give returns one on which no work is in flight.  pool_user

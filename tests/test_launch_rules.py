@@ -56,3 +56,31 @@ def test_one_thread_closes_a_face_where_groups_would_queue(lanes):
     assert lanes([129, 129], 16384, 16385, 80000) == [16, 1, 1]
     assert lanes([100, 100, 100], 16384, 16385) == [16, 1]
     assert lanes([16385], 128, 24577) == [256, 1]
+
+
+def test_streaming_stores(tmp_path):
+    exe = build(str(tmp_path), r"""
+#include "cdugks_host.h"
+#include <cstdio>
+#include <cstdlib>
+int main(int argc, char** argv) {
+    for (int k = 1; k + 3 < argc; k += 4) {
+        cdg::Resolved r{};
+        r.D = atoi(argv[k]);
+        r.storage = atoi(argv[k + 1]);
+        r.ne[0] = atoi(argv[k + 2]);
+        r.V = atoi(argv[k + 3]);
+        printf("%d ", cdg::fv_streams(r) ? 1 : 0);
+    }
+}
+""", [cd.LIB_PATH, "-Wl,-rpath," + os.path.dirname(cd.LIB_PATH)])
+
+    def ask(*problems):
+        args = [str(x) for p in problems for x in p]
+        return [int(x) for x in
+                subprocess.run([exe, *args], check=True, stdout=subprocess.PIPE, text=True).stdout.split()]
+
+    # dimension, storage form, faces of a row, velocities
+    assert ask((2, 0, 256, 784), (2, 0, 257, 784), (2, 0, 8, 4)) == [1, 0, 1]
+    assert ask((2, 1, 256, 4095), (2, 1, 256, 4096), (2, 1, 257, 4096), (2, 2, 256, 16641)) == [0, 1, 0, 1]
+    assert ask((3, 1, 64, 512), (3, 1, 65, 512), (3, 0, 24, 64)) == [1, 0, 1]
