@@ -331,8 +331,11 @@ int resolve(const cdugks_space* sp, const cdugks_velocity* ve, const cdugks_para
 // 16 x 16 or 19 x 10: FP64 1419 and 1376 us, FP32 723 and 677; 5 of 8 x 29:
 // 1286 and 734).  Face sums with and without the rule: 20^3 x 12^3 FP64 887
 // and 578 us, FP32 461 and 317; 33 x 33 x 20 x 10^3 FP64 1232 and 989; 30
-// drawn sizes, FP64 and FP32, 0.63 to 1.0 of the time, 0.90 on average.  Grids
-// in whole sectors (streaming stores) take columns of whole sectors.
+// drawn sizes, FP64 and FP32, 0.63 to 1.0 of the time, 0.90 on average.  The
+// faces of the single slope, of Dirichlet sides and of an acceleration cost
+// other amounts, but what a column saves is the same: over ten sizes in every
+// storage form 0.60 to 1.0 with each of the three, as without.  Grids in whole
+// sectors (streaming stores) take columns of whole sectors.
 static void choose_column(const Resolved& r, int (&column)[2]) {
     const int es = r.storage == CDUGKS_STORE_F64 ? 8 : 4, nf = es == 8 ? 2 : 1;
     auto waves = [](int n) { return (n + 63) / 64; };
@@ -721,9 +724,10 @@ int init_context(const cdugks_space* space, const cdugks_velocity* vel, const cd
     for (long long k = 0; k < (long long)r.D * r.N; ++k)
         if (!std::isfinite(u[k])) return fail(CDUGKS_ERR_INVALID, "u[%lld] is not finite", k);
 
-    // kernels reach into a velocity row by 32-bit byte offsets; the
-    // coefficients and face sums of rows past 4 GB (over 300 bytes per cell)
-    // exceed any device's memory
+    // Kernels reach into a velocity row by 32-bit byte offsets.  Rows of 4 GB
+    // (2^29 faces in FP64, 2^30 in FP32; two axes at least, as one holds 2^24
+    // cells) belong to problems of 449 GB (2-D FP64, 2 x 2 velocities; FP32
+    // 768 GB) and more, which the device cannot hold.
     if ((unsigned long long)(r.NE + 1) * (r.storage == CDUGKS_STORE_F64 ? 8 : 4) >= (1ULL << 32))
         return fail(CDUGKS_ERR_NOMEM, "velocity rows of %lld faces do not fit device memory", (long long)r.NE);
 

@@ -564,11 +564,7 @@ struct FaceCoef {
         return xu - hu2;
     }
     // phi at the face from phi_bar (eq. phibar inverted): g first, then b with
-    // the S_b source at the face evaluated with the face g.
-    __device__ __forceinline__ void invert(const Vel& v, double geq, double vg, double vb, double& gF,
-                                           double& bF) const {
-        invert_z(v, geq, z(v), vg, vb, gF, bF);
-    }
+    // the S_b source at the face evaluated with the face g and Z = z(v).
     __device__ __forceinline__ void invert_z(const Vel& v, double geq, double Z, double vg, double vb, double& gF,
                                              double& bF) const {
         double beq = (v.hx2 + cRT2) * geq;
@@ -584,10 +580,6 @@ struct FaceCoef {
 #pragma unroll
         for (int e = 0; e < D; ++e) au += a[e] * u[e];
         c2 = 0.5 * dt * inv2RT;
-    }
-    __device__ __forceinline__ void invert_accel(const Vel& v, double dt, double geq, double vg, double vb,
-                                                 double& gF, double& bF) const {
-        invert_accel_z(v, dt, geq, z(v), vg, vb, gF, bF);
     }
     __device__ __forceinline__ void invert_accel_z(const Vel& v, double dt, double geq, double Z, double vg,
                                                    double vb, double& gF, double& bF) const {
@@ -627,25 +619,13 @@ __device__ __forceinline__ double maxwellian(double A, double s, const double* u
 
 // The Maxwellian at FP32 accuracy, for the update kernel of the FP32 storage
 // forms (whose stored values carry a relative rounding of 2^-24): the exponent
-// is split in FP64 as -c2 s log2(e) = n + f with n an integer and |f| <= 1/2;
-// 2^f is the hardware FP32 base-2 exponential (within 1 ulp) of f rounded to
-// FP32 (an argument error below 2^-25), and 2^n is applied exactly.  The
+// is split in FP64 as -|xi - u|^2 s log2(e) = n + f with n an integer and |f| <=
+// 1/2; 2^f is the hardware FP32 base-2 exponential (within 1 ulp) of f rounded
+// to FP32 (an argument error below 2^-25), and 2^n is applied exactly.  The
 // relative error is below 1e-7, against about 1e-16 for the FP64 exponential
 // at a quarter of the instructions.  Exponents below -1500 give 0.
-template <int D>
-__device__ __forceinline__ double maxwellian_f32(double A, double s, const double* u, const Vel& v) {
-    double c2 = 0.0;
-#pragma unroll
-    for (int e = 0; e < D; ++e) {
-        const double x = v.xi[e] - u[e];
-        c2 += x * x;
-    }
-    const double t = fmin(fmax(-c2 * s * M_LOG2E, -1500.0), 1500.0);
-    const double n = rint(t);
-    return A * ldexp((double)__builtin_amdgcn_exp2f((float)(t - n)), (int)n);
-}
-// The same from Z = xi.u - |u|^2/2, which the face inversion and the S_b
-// source need anyway: |xi - u|^2 = 2 (|xi|^2/2 - Z), so the exponent takes one
+// The exponent comes from Z = xi.u - |u|^2/2, which the face inversion and the
+// S_b source need anyway: |xi - u|^2 = 2 (|xi|^2/2 - Z), so it takes one
 // subtraction instead of D differences and squares.  The rounding of the
 // expanded square (relative 1e-16 of |xi|^2 + |u|^2) stays far below the
 // FP32 accuracy of the result.
@@ -1117,15 +1097,6 @@ struct FaceSumKernel {
 // ---------------------------------------------------------------------------
 // cell closure: W^{n+1} = W^n - dt sum_d (G_right - G_left)/dx_d; coefs at n+1
 // ---------------------------------------------------------------------------
-// Part of the single-problem update kernel: each of a cell's update threads
-// (one per velocity slice) forms W^{n+1} and the coefficients it needs for
-// itself, and the one of slice 0 (store) writes them for the next step.  The
-// D + 2 flux moments of 2D faces are a few loads against hundreds of
-// velocities, where a launch of its own cost 4 us of a 52 us step of the Sod
-// tube and 13 us of 1.40 ms of the 256^2 x 28^2 step.  In the batched update
-// the same code raised the FP32 2-D class from 165 to 231 registers (3 waves
-// per SIMD to 2), so batches keep the launch (one for all problems, under 1%
-// of their step).  fl, fr: the cell's left and right faces.
 // The left and right faces of cell c along each d (periodic wrap at the right
 // end).  Cell and face indices fit 31 bits (checked at set-up).
 template <int D>
@@ -1142,6 +1113,15 @@ __device__ __forceinline__ void cell_faces(const Problem& P, unsigned c, unsigne
     }
 }
 
+// Part of the single-problem update kernel: each of a cell's update threads
+// (one per velocity slice) forms W^{n+1} and the coefficients it needs for
+// itself, and the one of slice 0 (store) writes them for the next step.  The
+// D + 2 flux moments of 2D faces are a few loads against hundreds of
+// velocities, where a launch of its own cost 4 us of a 52 us step of the Sod
+// tube and 13 us of 1.40 ms of the 256^2 x 28^2 step.  In the batched update
+// the same code raised the FP32 2-D class from 165 to 231 registers (3 waves
+// per SIMD to 2), so batches keep the launch (one for all problems, under 1%
+// of their step).  fl, fr: the cell's left and right faces.
 template <int D>
 __device__ __forceinline__ CellCoef cell_close(const Problem& P, long long c, const unsigned (&fl)[D],
                                                const unsigned (&fr)[D], bool store) {

@@ -31,7 +31,6 @@ enum { PF_A = 0, PF_INV2RT, PF_CRT2, PF_IG, PF_IB, PF_EB, PF_HU2, PF_U0, NFP = P
 // external acceleration a.
 enum { VE_XI0 = 0, VE_W = 3, VE_HX2 = 4, VE_LAM0 = 5, VE_WXI0 = 8, VE_WXX = 11, VE_AX = 20, NVEL = 21 };
 
-constexpr int MAX_NSUM = 9;  // 2D+3 face sums for D = 3
 // threads per workgroup of the update and closure kernels (the per-problem
 // thread ranges of batched closures start on multiples of it)
 constexpr int WG = 256;
@@ -154,10 +153,9 @@ hipError_t launch_cell_close_batched(const Problem* probs, const long long* offs
 int tile_blocks_per_cu(int D, int storage, bool update);
 
 // Face-sum tile shapes: cells per workgroup along x, y, z, one thread per
-// cell.  Shape 0 of each dimension plans the velocity split
-// and is the shape of batched launches; default_face_tile(D) is the one a single problem runs
-// unless the caller (cdugks_params.face_tile) or the autotuner chooses
-// another.  A cell's arithmetic does not depend on the tile it sits in (in
+// cell.  Shape 0 of each dimension plans the velocity split and is the shape of
+// batched launches; default_face_tile(D) is the one a single problem runs unless
+// the caller (cdugks_params.face_tile) or the autotuner chooses another.  A cell's arithmetic does not depend on the tile it sits in (in
 // 2-D every shape keeps its q-box slots in registers, see Geo), and the
 // velocity split is planned with shape 0, so every shape gives bitwise the
 // same result.  Shapes wider along x use more of each 128-byte line of a halo

@@ -10,7 +10,10 @@
 // Faces along d are indexed by the cell on their right on the extended grid
 // NE = prod_d (n_d + [outflow_d]).
 //
-// One step = three launches (four in a batch):
+// One step = three launches.  Four where the face sums are two (the z-march of
+// 3-D problems and of small 1-D and 2-D ones' split: face values, then their
+// sums) and in a batch (whose cells are closed in a launch of their own); five
+// in 3-D with BF16 tails, whose update is two:
 //   face_sums  (tile kernel) : quarter-step field phi_bar_plus (eq. phibarplus),
 //                              Van Leer slopes (eq. VanLeer) and slopes of slopes,
 //                              face value at the characteristic foot (eq. relation),

@@ -84,3 +84,19 @@ int main(int argc, char** argv) {
     assert ask((2, 0, 256, 784), (2, 0, 257, 784), (2, 0, 8, 4)) == [1, 0, 1]
     assert ask((2, 1, 256, 4095), (2, 1, 256, 4096), (2, 1, 257, 4096), (2, 2, 256, 16641)) == [0, 1, 0, 1]
     assert ask((3, 1, 64, 512), (3, 1, 65, 512), (3, 0, 24, 64)) == [1, 0, 1]
+
+
+@pytest.mark.parametrize("storage, n, bc", [
+    ("f64", [31, 2 ** 24], ["outflow", "periodic"]),
+    ("f64", [2 ** 15, 2 ** 14], ["periodic", "periodic"]),
+    ("f64", [1, 15, 2 ** 24], ["outflow", "outflow", "periodic"]),
+    ("f32", [63, 2 ** 24], ["outflow", "periodic"]),
+    ("f32", [2 ** 15, 2 ** 15], ["periodic", "periodic"]),
+])
+def test_velocity_rows_of_4_gb_belong_to_problems_no_device_holds(storage, n, bc):
+    # the smallest velocity grid on the fewest cells whose face rows reach 4 GB,
+    # the reach of the kernels' 32-bit offsets in a row
+    D = len(n)
+    p = dict(dim=D, n=n, lo=[0.0] * D, hi=[1.0] * D, bc=bc, nv=[2] * D, vmin=[-5.0] * D, vmax=[5.0] * D,
+             relax="tau", tau=1.0, storage=storage)
+    assert cd.cdugks_required_bytes(p) > 288 * 2 ** 30
