@@ -173,7 +173,9 @@ int cdugks_required_bytes(const cdugks_space* space, const cdugks_velocity* vel,
  * cdugks_required_bytes figure, 256-byte aligned) may be NULL, in which case
  * the library allocates (memory it releases while other contexts or servers
  * live on the device may stay with it, up to 1/32 of the device's, for the
- * next; it is given back with the last of them).  Validation failures return CDUGKS_ERR_INVALID:
+ * next of the same size; it is given back with the last of them, and when an
+ * allocation of the library needs it).  Validation failures return
+ * CDUGKS_ERR_INVALID:
  * dim outside 1..3, n < 1, nv < 2, Boole with nv != 4k+1, gamma outside
  * (1, 5/3], Pr <= 0, R <= 0, rho <= 0, T <= 0 (in a cell or a Dirichlet
  * state), an unknown boundary condition, a requested dt above the CFL
@@ -308,8 +310,10 @@ void cdugks_batch_destroy(cdugks_batch* batch);
  * Thread-safe. */
 typedef struct cdugks_server cdugks_server;
 
-/* chunk_steps: steps per admission round (rounded up to an even count, the
- * batch's graph chunk). */
+/* hbm_budget: device bytes of the requests running at once, each counted with
+ * its cdugks_required_bytes; memory the library keeps idle on the device is
+ * given back as far as an admission needs the room.  chunk_steps: steps per
+ * admission round (rounded up to an even count, the batch's graph chunk). */
 int cdugks_server_create(size_t hbm_budget, int max_active, int chunk_steps,
                          void* hip_stream, cdugks_server** out);
 /* Copies the request.  CDUGKS_ERR_TOO_LARGE if it can never fit the budget. */
